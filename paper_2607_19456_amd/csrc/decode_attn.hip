@@ -230,12 +230,39 @@ __device__ __forceinline__ int decode_rows(int32_t len_b, int n_max, bool app, i
 }
 
 // ---------------------------------------------------------------------------
-// KV append of T rows.  One workgroup per sequence; every thread reads len[b]
-// before the barrier, thread 0 writes it after, so no thread can see the new
-// value.  Rows r = 0..T-1 land at len[b] + r as long as they fit (the
-// single-row append applied T times).
+// KV append of T rows: rows r = 0..T-1 land at len[b] + r as long as they fit
+// (the single-row append applied T times).  In both caches the rows of one
+// (b, KV head) are one contiguous run on either side, so a slab's append is
+// two plain copies of cnt * d floats, in 16-byte pieces.
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(kThreads) void kv_append_kernel(
+// Piece u of a slab's append: its cnt*ck pieces of K, then its cnt*cv of V.
+__device__ __forceinline__ void append_piece(float* __restrict__ K, float* __restrict__ V,
+                                             const float* __restrict__ k_new,
+                                             const float* __restrict__ v_new, int64_t slab,
+                                             int64_t row0, int cnt, int T, int n_max, int ck,
+                                             int cv, int64_t u) {
+  const int64_t nk = (int64_t)cnt * ck;
+  if (u < nk) {
+    const u4* src = reinterpret_cast<const u4*>(k_new) + slab * T * ck + u;
+    reinterpret_cast<u4*>(K)[(slab * n_max + row0) * ck + u] = *src;
+  } else if (u - nk < (int64_t)cnt * cv) {
+    const u4* src = reinterpret_cast<const u4*>(v_new) + slab * T * cv + (u - nk);
+    reinterpret_cast<u4*>(V)[(slab * n_max + row0) * cv + (u - nk)] = *src;
+  }
+}
+
+// Few pieces per sequence: one launch, one workgroup per sequence.  Every
+// thread reads len[b] before the barrier, thread 0 writes it after, so no
+// thread can see the new value.  A workgroup's copy loop is bound by its
+// round trips to memory (16 KB each), so the line to the two launches below
+// lies where the loop costs as much as the second launch (measured inside a
+// graph, d = 128, with a small fill before each: 8 sequences x 4096 pieces
+// 5.5 us here and 5.6 in two launches, 2048 pieces 4.6 and 5.5, 8192 pieces
+// 7.5 and 5.5, 16384 pieces 11.0 and 5.9; 256 sequences x 4096 pieces 7.5
+// and 9.2).
+constexpr int64_t kAppendOneLaunch = 4096;
+constexpr int kAppendThreads = 1024;
+__global__ __launch_bounds__(kAppendThreads) void kv_append_kernel(
     float* __restrict__ K, float* __restrict__ V,
     const float* __restrict__ k_new, const float* __restrict__ v_new,
     int32_t* __restrict__ len, int h_kv, int n_max, int d_k, int d_v, int T) {
@@ -243,32 +270,47 @@ __global__ __launch_bounds__(kThreads) void kv_append_kernel(
   const int32_t t = len[b];
   const int cnt = (t >= 0 && t < n_max) ? min(T, n_max - t) : 0;
   if (cnt > 0) {
-    const int ck = d_k / 4, cv = d_v / 4;            // 16-byte chunks per row
-    const int per_row = ck + cv;
-    const int per_head = cnt * per_row;
-    const int total = h_kv * per_head;
-    for (int c = threadIdx.x; c < total; c += blockDim.x) {
+    const int ck = d_k / 4, cv = d_v / 4;            // 16-byte pieces per row
+    const int per_head = cnt * (ck + cv);
+    for (int c = threadIdx.x; c < h_kv * per_head; c += kAppendThreads) {
       const int g = c / per_head;
-      const int rem = c - g * per_head;
-      const int r = rem / per_row;
-      const int w = rem - r * per_row;
-      const int64_t slab = (int64_t)b * h_kv + g;
-      const int64_t src_row = slab * T + r;
-      const int64_t dst_row = slab * n_max + t + r;
-      if (w < ck) {
-        const u4* src = reinterpret_cast<const u4*>(k_new + src_row * d_k) + w;
-        u4* dst = reinterpret_cast<u4*>(K + dst_row * d_k) + w;
-        *dst = *src;
-      } else {
-        const int wv = w - ck;
-        const u4* src = reinterpret_cast<const u4*>(v_new + src_row * d_v) + wv;
-        u4* dst = reinterpret_cast<u4*>(V + dst_row * d_v) + wv;
-        *dst = *src;
-      }
+      append_piece(K, V, k_new, v_new, (int64_t)b * h_kv + g, t, cnt, T, n_max, ck, cv,
+                   c - g * per_head);
     }
   }
   __syncthreads();
   if (cnt > 0 && threadIdx.x == 0) len[b] = t + cnt;
+}
+
+// Many pieces: the copies spread over the whole chip, kAppendPieces pieces of
+// one slab per workgroup (their loads all in flight at once), and len is
+// advanced by a second launch, once every workgroup has read it.  Bound by
+// HBM: 8 sequences x 8 heads x 700 rows at d = 128 (92 MB read and written)
+// take 18 us, 5.0 TB/s, where one workgroup per sequence took 1200 us (four
+// round trips of 4 KB a microsecond each).
+constexpr int kAppendPieces = 4 * kThreads;
+__global__ __launch_bounds__(kThreads) void kv_append_copy_kernel(
+    float* __restrict__ K, float* __restrict__ V, const float* __restrict__ k_new,
+    const float* __restrict__ v_new, const int32_t* __restrict__ len, int64_t slabs, int h_kv,
+    int n_max, int ck, int cv, int T, int blocks_per_slab) {
+  const int64_t total = slabs * blocks_per_slab;
+  for (int64_t blk = blockIdx.x; blk < total; blk += gridDim.x) {
+    const int64_t slab = blk / blocks_per_slab;
+    const int64_t first = (blk - slab * blocks_per_slab) * kAppendPieces + threadIdx.x;
+    const int32_t t = len[slab / h_kv];
+    const int cnt = (t >= 0 && t < n_max) ? min(T, n_max - t) : 0;
+#pragma unroll
+    for (int x = 0; x < kAppendPieces / kThreads; ++x)
+      append_piece(K, V, k_new, v_new, slab, t, cnt, T, n_max, ck, cv, first + x * kThreads);
+  }
+}
+
+__global__ __launch_bounds__(kThreads) void kv_append_len_kernel(int32_t* __restrict__ len, int B,
+                                                                 int n_max, int T) {
+  const int b = blockIdx.x * kThreads + threadIdx.x;
+  if (b >= B) return;
+  const int32_t t = len[b];
+  if (t >= 0 && t < n_max) len[b] = t + min(T, n_max - t);
 }
 
 // ---------------------------------------------------------------------------
@@ -2060,8 +2102,21 @@ da_status da_kv_append_rows(float* K, float* V, const float* k_new, const float*
     return DA_ERR_ALIGN;
   hipStream_t s = static_cast<hipStream_t>(stream);
   (void)hipGetLastError();
-  hipLaunchKernelGGL(kv_append_kernel, dim3((unsigned)B), dim3(kThreads), 0, s, K, V, k_new,
-                     v_new, len, h_kv, n_max, d_k, d_v, T);
+  const int64_t per_slab = (int64_t)T * (d_k / 4 + d_v / 4);
+  if (h_kv * per_slab <= kAppendOneLaunch) {
+    hipLaunchKernelGGL(kv_append_kernel, dim3((unsigned)B), dim3(kAppendThreads), 0, s, K, V,
+                       k_new, v_new, len, h_kv, n_max, d_k, d_v, T);
+    return launch_status();
+  }
+  const int blocks_per_slab = (int)ceil_div(per_slab, kAppendPieces);
+  const int64_t slabs = (int64_t)B * h_kv;
+  const int64_t grid = std::min<int64_t>(slabs * blocks_per_slab, 1 << 20);
+  hipLaunchKernelGGL(kv_append_copy_kernel, dim3((unsigned)grid), dim3(kThreads), 0, s, K, V,
+                     k_new, v_new, len, slabs, h_kv, n_max, d_k / 4, d_v / 4, T, blocks_per_slab);
+  const da_status st = launch_status();
+  if (st != DA_OK) return st;
+  hipLaunchKernelGGL(kv_append_len_kernel, dim3((unsigned)ceil_div(B, kThreads)), dim3(kThreads),
+                     0, s, len, B, n_max, T);
   return launch_status();
 }
 
