@@ -1617,6 +1617,718 @@ __global__ __launch_bounds__(kThreads) void decode_merge_kernel(
 }
 
 // ---------------------------------------------------------------------------
+// Many query rows per KV head (prompt chunks, wide verification steps): the
+// chunk kernels.
+//
+// Above 32 query rows per KV head the decode is bound by the matrix cores,
+// and fp32 products run there at 1/16 of the 16-bit rate.  So a workgroup
+// takes a tile of QT = 32 * NW query rows of one KV head, stages 32 keys at a
+// time in LDS -- each fp32 value as the sum of two fp16 values -- and forms
+// every product from three 16-bit ones:
+//   x = s (h + l),  h = fp16(x / s),  l = fp16(x / s - h)
+//   x y = s_x s_y (h_x h_y + h_x l_y + l_x h_y),  sums in fp32.
+// Rounding to nearest leaves |x / s - h - l| <= 2^-24 |x / s| (half an fp32
+// ulp), and the term left out is below 2^-24 |x y|; sums have 24 roundings
+// per score where the fp32 instruction's have 64, and every 32 keys' share of
+// the output is summed apart before it is added.  Against 64 bits (relative
+// 2-norm, N(0, 1) inputs): 3.4e-7 where the fp32 products had 6.2e-7 (512
+// rows x 4 heads per KV head behind 1000-7600 keys, d = 128), 1.9e-7 / 2.1e-7
+// (1500 rows of an empty cache, d = 64), 4.9e-7 / 8.4e-7 (64 rows behind
+// 60000 keys).  The scales s are powers of two that put the operands into
+// fp16's range whatever their magnitude: one per query row (largest element in
+// [2^14, 2^15)), one per visit each for K and V, raised when a tile outgrows
+// it (its first tile's largest element in [2^11, 2^12)), and 2^7 for the
+// weights, which are at most 2^8 of their reference.  Elements far below
+// their scale's largest keep an absolute error of 2^-36 of it or less.  What
+// this cannot hold -- infinities and NaN, and staged parts of a tile (64
+// lanes' share) that are not zero but below 2^-13 of the visit's scale --
+// shows at a visit's end (a non-finite sum, or a flag set while staging), and
+// the visit is then formed again in plain fp32.
+//
+// Matrix-bound: 2 sequences x 32/8 heads x 512 rows behind 1000-7600 keys, d =
+// 128 (86 GFLOP; 105 us at the 16-bit rate with three products for one): 300
+// us, with the fp32 products in groups of 32 rows 940 us.  Prompt of 1500
+// rows x 16 heads, d = 64: 67 us from 237.  Of a tile's 6300 cycles per SIMD
+// (two waves) 3072 are matrix work; the rest is the waves' softmax and staging
+// where it finds no partner.  Few rows gain too (8 sequences x 64/8 heads x 8
+// rows behind 2000-8000 keys 119 -> 93 us; 5 rows behind 20000-32000 293 ->
+// 232), since a tile is read and staged once for all of a KV head's rows; a
+// single row per head (T = 1) with more than 32 heads per KV head does not (8
+// x 64/1 heads behind 9000-16000 keys: 54 us with two groups of 32, 69 here)
+// and keeps the groups of 32.
+//
+// Matrix layouts (v_mfma_f32_32x32x16_f16; lane = 0..63, i = lane % 32,
+// h = lane / 32): A holds row i, B column i, both k = 8h..8h+7; D holds
+// column i, rows 8(r/4) + 4h + r%4 in component r = 0..15.  Scores are
+// S[key][query] = K Q^T, so a lane's 16 scores belong to one query, and they
+// are the B operand of O^T[dim][query] += V^T[dim][key] P[key][query] as they
+// stand when its k-index 8h+j of step t means key 16t + 4h + j (+4 for
+// j >= 4): V is staged transposed in that key order.
+// ---------------------------------------------------------------------------
+typedef float f2 __attribute__((ext_vector_type(2)));
+typedef _Float16 h2 __attribute__((ext_vector_type(2)));
+typedef _Float16 h8 __attribute__((ext_vector_type(8)));
+typedef float f16v __attribute__((ext_vector_type(16)));
+
+constexpr int kChunkKeys = 32;          // keys per staged tile
+constexpr int kChunkMinRows = 33;       // query rows per KV head from which the chunk kernels run
+// Keys per scheduling unit of a query tile.
+constexpr int kChunkUnit = 128;
+constexpr float kChunkLift = 128.f;     // weights are staged times this
+
+// Eight fp32 values times a power of two as the fp16 sum h + l.  (Packed
+// conversions: the mixed-precision multiply-adds that would do it in fewer
+// instructions take 10 cycles each here, these 4.)
+__device__ __forceinline__ void split8(const float (&x)[8], float s, h8& hi, h8& lo) {
+#pragma clang fp contract(off)
+#pragma unroll
+  for (int e = 0; e < 8; e += 2) {
+    const f2 v = f2{x[e], x[e + 1]} * s;
+    const h2 h = __builtin_convertvector(v, h2);
+    f2 r = v - __builtin_convertvector(h, f2);
+    const h2 l = __builtin_convertvector(r, h2);
+    hi[e] = h[0];
+    hi[e + 1] = h[1];
+    lo[e] = l[0];
+    lo[e + 1] = l[1];
+  }
+}
+
+// (maximum: a NaN stays, and no operand needs quieting first.)
+__device__ __forceinline__ float max2(float a, float b) {
+  return __builtin_elementwise_maximum(a, b);
+}
+__device__ __forceinline__ float max_abs8(const float (&x)[8]) {
+  float m = max2(max2(fabsf(x[0]), fabsf(x[1])), fabsf(x[2]));
+  m = max2(max2(m, fabsf(x[3])), fabsf(x[4]));
+  return max2(max2(m, fabsf(x[5])), max2(fabsf(x[6]), fabsf(x[7])));
+}
+
+// Exponent field of |x|, kept where the scales below are normal numbers.
+__device__ __forceinline__ int exponent_of(float x) {
+  const int e = (int)((__float_as_uint(x) >> 23) & 255u);
+  return e < 32 ? 32 : (e > 254 ? 254 : e);
+}
+// 2^(p - (e - 127)): takes a value with exponent field e to [2^p, 2^(p+1)).
+__device__ __forceinline__ float scale_to(int e, int p) {
+  return __uint_as_float((unsigned)(254 + p - e) << 23);
+}
+// Its inverse.
+__device__ __forceinline__ float scale_from(int e, int p) {
+  return __uint_as_float((unsigned)(e - p) << 23);
+}
+
+template <int CTRL>
+__device__ __forceinline__ float dpp_max(float x) {
+  return max2(x, __uint_as_float(__builtin_amdgcn_update_dpp(
+                     0, (int)__float_as_uint(x), CTRL, 0xf, 0xf, true)));
+}
+__device__ __forceinline__ float max_over_wave(float x) {
+  x = dpp_max<0xB1>(x);                                 // quad: lane ^ 1
+  x = dpp_max<0x4E>(x);                                 // quad: lane ^ 2
+  x = dpp_max<0x141>(x);                                // mirrored in 8
+  x = dpp_max<0x140>(x);                                // mirrored in 16
+  const unsigned u = __float_as_uint(x);
+  const auto a = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+  x = max2(__uint_as_float(a[0]), __uint_as_float(a[1]));
+  const unsigned v = __float_as_uint(x);
+  const auto b = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+  return max2(__uint_as_float(b[0]), __uint_as_float(b[1]));
+}
+__device__ __forceinline__ float max_over_halves(float x) {
+  const unsigned u = __float_as_uint(x);
+  const auto a = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+  return max2(__uint_as_float(a[0]), __uint_as_float(a[1]));
+}
+// A value that all lanes hold, as a scalar (what follows from it stays on the
+// scalar unit and branches on it are not per lane).
+__device__ __forceinline__ int uniform(int x) { return __builtin_amdgcn_readfirstlane(x); }
+__device__ __forceinline__ int64_t uniform(int64_t x) {
+  const unsigned lo = (unsigned)uniform((int)x), hi = (unsigned)uniform((int)(x >> 32));
+  return (int64_t)((uint64_t)hi << 32 | lo);
+}
+__device__ __forceinline__ float sum_over_halves(float x) {
+  const unsigned u = __float_as_uint(x);
+  const auto a = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+  return __uint_as_float(a[0]) + __uint_as_float(a[1]);
+}
+
+// Sizes and pointers of a chunk launch.  R query rows per KV head in nqt
+// tiles of QT; row x of a KV head is position x % T of one of its heads.
+struct ChunkArgs {
+  const float* __restrict__ q;
+  float* __restrict__ K;
+  float* __restrict__ V;
+  const float* __restrict__ k_new;
+  const float* __restrict__ v_new;
+  const int32_t* __restrict__ len;
+  float qscale;
+  int B, h_kv, n_max, T, R, nqt, unit, J;
+  unsigned* __restrict__ nvis;
+  float2* __restrict__ ws_ml;
+  float* __restrict__ ws_acc;
+};
+
+// Keys that query tile qt of sequence b sees, as a count from key 0.
+__device__ __forceinline__ int chunk_keys(const ChunkArgs& a, int32_t len_b, int qt, int QT) {
+  const bool app = a.k_new != nullptr;
+  const int n = decode_rows(len_b, a.n_max, app, a.T);
+  const int lo = qt * QT;
+  const int hi = min(a.R, lo + QT) - 1;
+  const int rmax = hi / a.T != lo / a.T ? a.T - 1 : hi % a.T;
+  const int64_t pos0 = app ? (int64_t)len_b : (int64_t)n - a.T;
+  const int64_t keys = std::min<int64_t>(pos0 + rmax, n - 1) + 1;
+  return keys > 0 ? (int)keys : 0;
+}
+
+// The schedule: the units (a.unit keys) of all items (sequence b, query tile
+// qt, KV head g; in that order) form one space of U units cut into G equal
+// contiguous ranges, one per workgroup, each (range, item) meeting a visit
+// with a partial slot of its own, as for the persistent decode.  The
+// workgroups that take part are as few as keep every item's visits within
+// its J slots: an item of nt units meets at most floor((nt - 1) / (U / G)) + 2
+// ranges.
+template <int DK, int DV, int NW>
+__global__ __launch_bounds__(64 * NW, (DK + DV <= 256 ? 2 : 1))
+void chunk_partial_kernel(const ChunkArgs a) {
+  constexpr int NT = 64 * NW;
+  constexpr int QT = 32 * NW;
+  constexpr int KC = DK / 8;                            // 8-float pieces of a K row
+  constexpr int KU = kChunkKeys * KC;                   // staging units of K: (key, piece)
+  constexpr int VU = DV * 4;                            // of V: (dim, 8 keys)
+  constexpr int UN = KU + VU;
+  constexpr int UPT = (UN + NT - 1) / NT;
+  constexpr int kKPiece = 16 * (kChunkKeys + 1);        // bytes between K pieces
+  constexpr int kKPlane = KC * kKPiece;
+  constexpr int kVPlane = 64 * DV;
+  // K of the current and the next tile; V of the previous one as well where
+  // waves update late (see `early`).
+  constexpr int kVBufs = NW == 8 ? 3 : 2;
+  __shared__ __align__(16) char sh_k[2][2 * kKPlane];
+  __shared__ __align__(16) char sh_v[kVBufs][2 * kVPlane];
+  __shared__ int sh_need[2][2];                         // largest exponent of K, V staged
+  __shared__ int sh_bad;
+
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int i = lane & 31;
+  const int h = lane >> 5;
+  const bool app = a.k_new != nullptr;
+
+  // The fused append's copies, spread over the workgroups in blocks of four
+  // pieces a thread; the decode never reads those rows from the cache.
+  if (app) {
+    const int per_slab = (a.T * (DK / 4 + DV / 4) + 4 * NT - 1) / (4 * NT);
+    for (int64_t blk = blockIdx.x; blk < (int64_t)a.B * a.h_kv * per_slab; blk += gridDim.x) {
+      const int64_t slab = blk / per_slab;
+      const int32_t t = a.len[slab / a.h_kv];
+      const int cnt = appended_rows(app, t, a.n_max, a.T);
+#pragma unroll
+      for (int x = 0; x < 4; ++x)
+        append_piece(a.K, a.V, a.k_new, a.v_new, slab, t, cnt, a.T, a.n_max, DK / 4, DV / 4,
+                     (blk - slab * per_slab) * (4 * NT) + x * NT + tid);
+    }
+  }
+
+  // Every wave derives the schedule by itself.
+  const int entries = a.B * a.nqt;
+  auto units_of = [&](int e) {
+    const int b = e / a.nqt;
+    return (chunk_keys(a, a.len[b], e - b * a.nqt, QT) + a.unit - 1) / a.unit;
+  };
+  int64_t U = 0;
+  int nt_max = 0;
+  for (int e0 = 0; e0 < entries; e0 += 64) {
+    const int e = e0 + lane;
+    const int v = e < entries ? units_of(e) : 0;
+    U += __shfl(wave_incl_scan(v, lane), 63);
+    nt_max = max(nt_max, (int)max_over_wave((float)v));   // (exact below 2^24 units)
+  }
+  U = uniform(U) * a.h_kv;
+  nt_max = uniform(nt_max);
+  int G = (int)gridDim.x;
+  if (nt_max > a.J) G = (int)std::max<int64_t>(1, std::min<int64_t>(G, U * (a.J - 2) / nt_max));
+  if ((int)blockIdx.x >= G) return;
+  int64_t u = (int64_t)blockIdx.x * U / G;
+  const int64_t u_hi = (int64_t)(blockIdx.x + 1) * U / G;
+  if (u >= u_hi) return;
+  // The entry that holds unit u.
+  int ent = 0, nt = 0;
+  int64_t first = 0;                                    // first unit of the entry
+  for (int e0 = 0; e0 < entries; e0 += 64) {
+    const int e = e0 + lane;
+    const int v = e < entries ? units_of(e) : 0;
+    const int64_t incl = wave_incl_scan(v, lane) * a.h_kv;
+    const unsigned long long m = __ballot(first + incl > u);
+    if (m) {
+      const int f = __ffsll((long long)m) - 1;
+      ent = e0 + f;
+      nt = __shfl(v, f);
+      first += __shfl(incl, f) - (int64_t)nt * a.h_kv;
+      break;
+    }
+    first += __shfl(incl, 63);
+  }
+
+  while (true) {
+    ent = uniform(ent);
+    nt = uniform(nt);
+    first = uniform(first);
+    u = uniform(u);
+    const int b = ent / a.nqt;
+    const int qt = ent - b * a.nqt;
+    const int g = (int)((u - first) / nt);
+    const int64_t P = first + (int64_t)g * nt;          // the item's first unit
+    const int64_t ue = std::min<int64_t>(u_hi, P + nt);
+    const int j = static_slot(P, u, U, G, (int)blockIdx.x);
+    const int nv = static_visits(P, nt, U, G);
+    const int32_t len_b = a.len[b];
+    const int n = decode_rows(len_b, a.n_max, app, a.T);
+    const int last_row = n - 1;
+    const int key0 = uniform((int)(u - P) * a.unit);
+    const int key1 = uniform(min((int)std::min<int64_t>((ue - P) * a.unit, n),
+                                 chunk_keys(a, len_b, qt, QT)));
+    const int64_t slab = (int64_t)b * a.h_kv + g;
+    const int new_cnt = appended_rows(app, len_b, a.n_max, a.T);
+    const int new_lo = new_cnt > 0 ? len_b : n;
+    const float* Ks = a.K + slab * a.n_max * DK;
+    const float* Vs = a.V + slab * a.n_max * DV;
+    const float* Kn = app ? a.k_new + slab * a.T * DK : nullptr;
+    const float* Vn = app ? a.v_new + slab * a.T * DV : nullptr;
+
+    // This lane's query row (column i of its wave's block).
+    const int x = qt * QT + 32 * wave + i;
+    const bool valid = x < a.R;
+    const int64_t row = slab * a.R + x;
+    int lim = -1;
+    if (valid) {
+      const int64_t pos0 = app ? (int64_t)len_b : (int64_t)n - a.T;
+      lim = (int)std::max<int64_t>(-1, std::min<int64_t>(pos0 + x % a.T, last_row));
+    }
+    // Last key any / every row of the wave sees.
+    int lim_max = (int)max_over_wave((float)lim);
+    int lim_min = -(int)max_over_wave(valid ? -(float)lim : -2147483648.f);
+    if (a.n_max > (1 << 24)) {                          // not exact as floats
+      lim_max = key1;
+      lim_min = -1;
+    }
+    lim_max = uniform(lim_max);
+    lim_min = uniform(lim_min);
+
+    // ---- tile loads: staging unit (tid + y*NT) of the tile at key kt.  A
+    // wave's 64 units are rows uw/KC.. of K (uw its first unit), or 64 dims of
+    // one 8-key group of V.
+    float raw[UPT][8];
+    const int lkey = lane / KC, lc = lane % KC;
+    // (Settled at compile time where K's and V's units fill whole rounds.)
+    auto unit_k = [&](int y) {
+      if constexpr (KU % NT == 0) return y < KU / NT;
+      else return y * NT + wave * 64 < KU;
+    };
+    auto unit_v = [&](int y) {
+      if constexpr (KU % NT == 0 && UN % NT == 0) return y >= KU / NT;
+      else return !unit_k(y) && y * NT + wave * 64 < UN;
+    };
+    auto load_tile_raw = [&](int kt) {
+      const bool plain = kt + kChunkKeys <= new_lo;
+      if (plain || (kt >= new_lo && kt + kChunkKeys <= new_lo + new_cnt)) {
+        const float* Kb = plain ? Ks + (int64_t)kt * DK : Kn + (int64_t)(kt - new_lo) * DK;
+        const float* Vb = plain ? Vs + (int64_t)kt * DV : Vn + (int64_t)(kt - new_lo) * DV;
+#pragma unroll
+        for (int y = 0; y < UPT; ++y) {
+          const int uw = y * NT + wave * 64;
+          if (unit_k(y)) {
+            const float* p = Kb + (uw / KC) * DK;
+            const f4 v0 = load4(p + (unsigned)(lkey * DK + 8 * lc));
+            const f4 v1 = load4(p + (unsigned)(lkey * DK + 8 * lc + 4));
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+              raw[y][e] = v0[e];
+              raw[y][4 + e] = v1[e];
+            }
+          } else if (unit_v(y)) {
+            const int kg = (uw - KU) / DV;
+            const float* p = Vb + (16 * (kg >> 1) + 4 * (kg & 1)) * DV + (uw - KU) % DV;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) raw[y][e] = (p + ((e & 3) + 8 * (e >> 2)) * DV)[(unsigned)lane];
+          }
+        }
+        return;
+      }
+      // Rows past the end clamp to the last row, appended rows come from
+      // k_new / v_new.  (The lane's indices are made opaque so that this path's
+      // addresses are formed inside it.)
+      int ln = lane;
+      asm volatile("" : "+v"(ln));
+      auto at = [&](int key, const float* base, const float* nbase, int D) {
+        const int r = min(kt + key, last_row);
+        return (unsigned)(r - new_lo) < (unsigned)new_cnt ? nbase + (int64_t)(r - new_lo) * D
+                                                          : base + (int64_t)r * D;
+      };
+#pragma unroll
+      for (int y = 0; y < UPT; ++y) {
+        const int uw = y * NT + wave * 64;
+        if (unit_k(y)) {
+          const float* p = at(uw / KC + ln / KC, Ks, Kn, DK) + 8 * (ln % KC);
+          const f4 v0 = load4(p), v1 = load4(p + 4);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            raw[y][e] = v0[e];
+            raw[y][4 + e] = v1[e];
+          }
+        } else if (unit_v(y)) {
+          const int kg = (uw - KU) / DV;
+#pragma unroll
+          for (int e = 0; e < 8; ++e)
+            raw[y][e] = at(16 * (kg >> 1) + 4 * (kg & 1) + (e & 3) + 8 * (e >> 2), Vs, Vn,
+                           DV)[(uw - KU) % DV + ln];
+        }
+      }
+    };
+    // ---- raw -> LDS with the visit's exponents xe (K, V).  Notes parts that
+    // outgrow them (for the next tile: see the loop) or fall far below.
+    int xe[2] = {32, 32};
+    auto stage = [&](int buf, int vbuf) {
+#pragma unroll
+      for (int y = 0; y < UPT; ++y) {
+        const int uw = y * NT + wave * 64;
+        if (!unit_k(y) && !unit_v(y)) continue;
+        const int v = unit_k(y) ? 0 : 1;
+        const float m = max_abs8(raw[y]);
+        if (__any(!(m < scale_from(min(xe[v] + 4, 255), 0))))
+          atomicMax(&sh_need[buf][v], exponent_of(m));
+        if (!__any(!(m < scale_from(xe[v] - 13, 0))) && __any(m > 0.f)) sh_bad = 1;
+        h8 hi, lo;
+        split8(raw[y], scale_to(xe[v], 11), hi, lo);
+        if (!v) {
+          char* base = sh_k[buf] + 16 * (uw / KC) + (lc * kKPiece + 16 * lkey);
+          *reinterpret_cast<h8*>(base) = hi;
+          *reinterpret_cast<h8*>(base + kKPlane) = lo;
+        } else {
+          char* base = sh_v[vbuf] + 16 * (uw - KU) + 16 * lane;
+          *reinterpret_cast<h8*>(base) = hi;
+          *reinterpret_cast<h8*>(base + kVPlane) = lo;
+        }
+      }
+    };
+
+    if (tid < 4) sh_need[tid >> 1][tid & 1] = 0;
+    if (tid == 4) sh_bad = 0;
+    load_tile_raw(key0);
+
+    // ---- q of the wave's rows, scaled into base-2 units and to its row's
+    // power of two, as fp16 sums: the B operand of the scores.
+    h8 qh[DK / 16], ql[DK / 16];
+    float fq;
+    {
+      const float* qr = a.q + row * DK + 8 * h;
+      float qv[DK / 16][8];
+      float m = 0.f;
+#pragma unroll
+      for (int t = 0; t < DK / 16; ++t) {
+        f4 v0 = f4{0.f, 0.f, 0.f, 0.f}, v1 = v0;
+        if (valid) {
+          v0 = load4(qr + 16 * t);
+          v1 = load4(qr + 16 * t + 4);
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          qv[t][e] = v0[e] * a.qscale;
+          qv[t][4 + e] = v1[e] * a.qscale;
+        }
+        m = fmaxf(m, max_abs8(qv[t]));
+      }
+      const int ex = exponent_of(max_over_halves(m));
+      const float s = scale_to(ex, 14);
+      fq = scale_from(ex, 14);
+#pragma unroll
+      for (int t = 0; t < DK / 16; ++t) split8(qv[t], s, qh[t], ql[t]);
+    }
+    // The first tile sets the exponents.
+    __syncthreads();                                    // sh_need, sh_bad cleared
+#pragma unroll
+    for (int y = 0; y < UPT; ++y) {
+      if (!unit_k(y) && !unit_v(y)) continue;
+      const int ex = exponent_of(max_over_wave(max_abs8(raw[y])));
+      if (lane == 0) atomicMax(&sh_need[0][unit_k(y) ? 0 : 1], ex);
+    }
+    __syncthreads();
+    xe[0] = __builtin_amdgcn_readfirstlane(sh_need[0][0]);
+    xe[1] = __builtin_amdgcn_readfirstlane(sh_need[0][1]);
+    stage(0, 0);
+    if (key0 + kChunkKeys < key1) load_tile_raw(key0 + kChunkKeys);
+    __syncthreads();
+
+    float m_run = -INFINITY, l_run = 0.f;
+    f16v acc[DV / 32];
+#pragma unroll
+    for (int c = 0; c < DV / 32; ++c)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[c][r] = 0.f;
+
+    bool odd = false;
+    // O^T += V^T P for the tile in V buffer vbuf; a 32-dim block's share is
+    // added while the next block's products run.
+    h8 ph[2], pl[2];
+    auto update = [&](int vbuf) {
+      const char* vb = sh_v[vbuf] + 16 * (h * DV + i);
+      h8 vh[2], vl[2];
+      auto read_v = [&](int x) {                        // step x % 2 of dims 32 (x / 2)..
+        const char* p = vb + 16 * (2 * (x & 1) * DV + 32 * (x >> 1));
+        vh[x & 1] = *reinterpret_cast<const h8*>(p);
+        vl[x & 1] = *reinterpret_cast<const h8*>(p + kVPlane);
+      };
+      read_v(0);
+      f16v o[2];
+#pragma unroll
+      for (int x = 0; x < DV / 16; ++x) {
+        const int t = x & 1, c = x >> 1;
+        if (x + 1 < DV / 16) read_v(x + 1);
+        if (t == 0)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) o[c & 1][r] = 0.f;
+        __builtin_amdgcn_sched_barrier(0);
+        o[c & 1] = __builtin_amdgcn_mfma_f32_32x32x16_f16(vl[t], ph[t], o[c & 1], 0, 0, 0);
+        o[c & 1] = __builtin_amdgcn_mfma_f32_32x32x16_f16(vh[t], pl[t], o[c & 1], 0, 0, 0);
+        o[c & 1] = __builtin_amdgcn_mfma_f32_32x32x16_f16(vh[t], ph[t], o[c & 1], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        if (t == 0 && c > 0) acc[c - 1] += o[(c - 1) & 1];
+      }
+      acc[DV / 32 - 1] += o[(DV / 32 - 1) & 1];
+    };
+    // The two waves of a SIMD go through a tile half a turn apart, so that
+    // one's softmax and staging (vector work) run beside the other's products:
+    // late waves form scores, weights and update of a tile and stage the next
+    // one; early waves start with the update of the tile before, stage, and
+    // form scores and weights.
+    const bool early = NW == 8 && wave < 4;
+    bool pending = false;                               // early: ph, pl wait for their update
+    int buf = 0, vbuf = 0;
+    auto vnext = [](int x) { return x == kVBufs - 1 ? 0 : x + 1; };
+    for (int kt = key0; kt < key1; kt += kChunkKeys, buf ^= 1, vbuf = vnext(vbuf)) {
+      if (pending) {
+        update(vbuf == 0 ? kVBufs - 1 : vbuf - 1);
+        pending = false;
+      }
+      // A tile of larger values than its exponent holds: raise that, rescale
+      // the sums (V), load and stage the tile again.  (Every wave reads the
+      // same numbers: their writers passed the last barrier, the next ones of
+      // this parity wait for the next.)
+      const int nk = __builtin_amdgcn_readfirstlane(sh_need[buf][0]);
+      const int nvx = __builtin_amdgcn_readfirstlane(sh_need[buf][1]);
+      if (nk > xe[0] + 3 || nvx > xe[1] + 3) {
+        if (nvx > xe[1] + 3) {
+          const int d = nvx - xe[1];
+          const float f = d > 100 ? 0.f : scale_to(127 + d, 0);
+          odd = odd || d > 100;
+#pragma unroll
+          for (int c = 0; c < DV / 32; ++c)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[c][r] *= f;
+          xe[1] = nvx;
+        }
+        xe[0] = max(xe[0], nk);
+        __syncthreads();                                // both read by every wave
+        load_tile_raw(kt);
+        stage(buf, vbuf);
+        if (kt + kChunkKeys < key1) load_tile_raw(kt + kChunkKeys);
+        __syncthreads();
+      }
+      const float fs = fq * scale_from(xe[0], 11);
+      const bool more = kt + kChunkKeys < key1;
+      auto stage_next = [&] {
+        stage(buf ^ 1, vnext(vbuf));
+        if (kt + 2 * kChunkKeys < key1) load_tile_raw(kt + 2 * kChunkKeys);
+      };
+      if (early && more) stage_next();
+      if (kt <= lim_max) {
+        const char* kb = sh_k[buf] + h * kKPiece + 16 * i;
+        f16v s;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) s[r] = 0.f;
+        // (Each step's operands are read a step ahead of their products.)
+        h8 kh[2], kl[2];
+        auto read_k = [&](int t) {
+          kh[t & 1] = *reinterpret_cast<const h8*>(kb + 2 * t * kKPiece);
+          kl[t & 1] = *reinterpret_cast<const h8*>(kb + 2 * t * kKPiece + kKPlane);
+        };
+        read_k(0);
+#pragma unroll
+        for (int t = 0; t < DK / 16; ++t) {
+          if (t + 1 < DK / 16) read_k(t + 1);
+          __builtin_amdgcn_sched_barrier(0);
+          s = __builtin_amdgcn_mfma_f32_32x32x16_f16(kl[t & 1], qh[t], s, 0, 0, 0);
+          s = __builtin_amdgcn_mfma_f32_32x32x16_f16(kh[t & 1], ql[t], s, 0, 0, 0);
+          s = __builtin_amdgcn_mfma_f32_32x32x16_f16(kh[t & 1], qh[t], s, 0, 0, 0);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+        if (kt + kChunkKeys - 1 > lim_min) {
+          const int seen = lim - kt - 4 * h;
+#pragma unroll
+          for (int r = 0; r < 16; ++r)
+            if (8 * (r / 4) + (r & 3) > seen) s[r] = -INFINITY;
+        }
+        float tm = max2(max2(s[0], s[1]), s[2]);
+#pragma unroll
+        for (int r = 3; r < 15; r += 2) tm = max2(max2(tm, s[r]), s[r + 1]);
+        tm = max_over_halves(max2(tm, s[15])) * fs;
+        const bool bump = tm > m_run + kLazyMax;
+        if (__any(bump)) {
+          const float m_new = bump ? tm : m_run;
+          const float alpha = bump ? fast_exp2(m_run - m_new) : 1.f;
+          l_run *= alpha;
+#pragma unroll
+          for (int c = 0; c < DV / 32; ++c)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[c][r] *= alpha;
+          m_run = m_new;
+        }
+        // A row that has seen no key yet exponentiates against 0.
+        const float m_ref = m_run == -INFINITY ? 0.f : m_run;
+        float psum = 0.f;
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+          float p[8];
+#pragma unroll
+          for (int e = 0; e < 8; ++e) p[e] = fast_exp2(__builtin_fmaf(s[8 * t + e], fs, -m_ref));
+          psum += ((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7]));
+          split8(p, kChunkLift, ph[t], pl[t]);
+        }
+        l_run += psum;
+        if (early) pending = true;
+        else update(vbuf);
+      }
+      if (!early && more) stage_next();
+      __syncthreads();
+    }
+
+    if (pending) update(vbuf == 0 ? kVBufs - 1 : vbuf - 1);
+
+    // ---- the visit's partial.
+    float L = sum_over_halves(l_run);
+    float of = scale_from(xe[1], 11) * (1.f / kChunkLift);
+    odd = odd || sh_bad != 0;
+    {
+      // A sum that is not finite stays so under this one (x - x is 0 or NaN).
+      float z = L - L;
+#pragma unroll
+      for (int c = 0; c < DV / 32; ++c)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) z += acc[c][r] - acc[c][r];
+      odd = odd || (valid && !(z == 0.f));
+    }
+    if (__any(odd)) {
+      // In plain fp32, one key after the other: both halves of a row's lanes
+      // form half of its score, and each sums the dims it holds.
+      L = 0.f;
+      m_run = -INFINITY;
+      of = 1.f;
+#pragma unroll
+      for (int c = 0; c < DV / 32; ++c)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[c][r] = 0.f;
+      const float* qr = a.q + (valid ? row : slab * a.R) * DK + h * (DK / 2);
+      for (int key = key0; key < key1; ++key) {
+        const bool isnew = (unsigned)(key - new_lo) < (unsigned)new_cnt;
+        const float* kr = isnew ? Kn + (int64_t)(key - new_lo) * DK : Ks + (int64_t)key * DK;
+        const float* vr = isnew ? Vn + (int64_t)(key - new_lo) * DV : Vs + (int64_t)key * DV;
+        float s = 0.f;
+#pragma unroll 4
+        for (int d = 0; d < DK / 2; ++d)
+          s = __builtin_fmaf(qr[d] * a.qscale, kr[h * (DK / 2) + d], s);
+        s = sum_over_halves(s);
+        if (key <= lim) {
+          if (s > m_run) {
+            const float alpha = fast_exp2(m_run - s);   // 0 for the first
+            L *= alpha;
+#pragma unroll
+            for (int c = 0; c < DV / 32; ++c)
+#pragma unroll
+              for (int r = 0; r < 16; ++r) acc[c][r] *= alpha;
+            m_run = s;
+          }
+          // (A NaN score makes the row NaN; scores of -inf have no weight.)
+          const float p = s == -INFINITY ? 0.f : fast_exp2(s - m_run);
+          L += p;
+#pragma unroll
+          for (int c = 0; c < DV / 32; ++c)
+#pragma unroll
+            for (int r = 0; r < 16; ++r)
+              acc[c][r] = __builtin_fmaf(p, vr[32 * c + 8 * (r / 4) + 4 * h + (r & 3)], acc[c][r]);
+        }
+      }
+    }
+    if (valid) {
+      const int64_t slot = row * a.J + j;
+      if (h == 0) {
+        a.ws_ml[slot] = make_float2(m_run, L);
+        if (j == 0) a.nvis[row] = (unsigned)nv;
+      }
+      float* dst = a.ws_acc + slot * DV + 4 * h;
+#pragma unroll
+      for (int c = 0; c < DV / 32; ++c)
+#pragma unroll
+        for (int rb = 0; rb < 4; ++rb)
+          *reinterpret_cast<f4*>(dst + 32 * c + 8 * rb) =
+              f4{acc[c][4 * rb], acc[c][4 * rb + 1], acc[c][4 * rb + 2], acc[c][4 * rb + 3]} * of;
+    }
+
+    u = ue;
+    if (u >= u_hi) break;
+    // The next item: the entry's next KV head, or the next entry with units.
+    if (u >= first + (int64_t)nt * a.h_kv) {
+      first += (int64_t)nt * a.h_kv;
+      do nt = units_of(++ent);
+      while (nt == 0);
+    }
+    __syncthreads();                                    // LDS of this visit is free
+  }
+}
+
+// Combines the visits of every query row (see the merge above) and clears the
+// row's visit count; a row without visits is zero.  The workgroups share
+// nothing, so each takes as many rows as its lanes cover.  After a fused
+// append the first workgroup advances len (no workgroup of this launch reads
+// it).
+template <int DV>
+__global__ __launch_bounds__(kThreads) void chunk_merge_kernel(
+    float* __restrict__ out, const float2* __restrict__ ws_ml, const float* __restrict__ ws_acc,
+    unsigned* __restrict__ nvis, int64_t rows, int J, int32_t* __restrict__ len_bump, int B,
+    int n_max, int T) {
+  constexpr int kCols = DV / 4;
+  const int64_t row = (int64_t)blockIdx.x * (kThreads / kCols) + threadIdx.x / kCols;
+  const int ch = threadIdx.x % kCols;
+  if (row < rows) {
+    const int nv = min((int)nvis[row], J);
+    const float2* ml = ws_ml + row * J;
+    const float* acc = ws_acc + row * J * DV + 4 * ch;
+    float m = -INFINITY, l = 0.f;
+    f4 o = f4{0.f, 0.f, 0.f, 0.f};
+    for (int j = 0; j < nv; ++j) {
+      const float2 st = ml[j];
+      const f4 v = load4(acc + (int64_t)j * DV);
+      if (st.x == -INFINITY && st.y == 0.f) continue;   // a visit that saw no key
+      const float mn = fmaxf(m, st.x);
+      const float wo = mn == m ? 1.f : fast_exp2(m - mn);
+      const float wn = mn == st.x ? 1.f : fast_exp2(st.x - mn);
+      l = l * wo + st.y * wn;
+      o = o * wo + v * wn;
+      m = mn;
+    }
+    *reinterpret_cast<f4*>(out + row * DV + 4 * ch) =
+        l == 0.f ? f4{0.f, 0.f, 0.f, 0.f} : o / l;
+    // (All lanes of a row are in one wave and have read the count.)
+    if (ch == 0) nvis[row] = 0u;
+  }
+  if (len_bump && blockIdx.x == 0)
+    for (int b = threadIdx.x; b < B; b += kThreads) {
+      const int32_t t = len_bump[b];
+      if (t >= 0 && t < n_max) len_bump[b] = t + min(T, n_max - t);
+    }
+}
+
+// ---------------------------------------------------------------------------
 // Host side: validation, sizing, launches.
 // ---------------------------------------------------------------------------
 struct Plan {
@@ -1632,6 +2344,7 @@ struct Plan {
   int merge_heads;    // query heads per slab the merge covers
   bool single_chunk;  // every slab fits in one chunk (direct form possible)
   bool two_waves;     // whole-slab static ranges at two workgroups per CU
+  bool chunked;       // the chunk kernels ran (set by the call, not by the plan)
   size_t line_bytes, counter_bytes, ml_bytes, bytes;
 };
 
@@ -1704,6 +2417,7 @@ da_status make_plan(int B, int h_q, int h_kv, int n_max, int d_k, int d_v, int c
     chunk_rows = (int)std::min<int64_t>(chunk_rows, whole);
   }
   if (chunk_rows < kChunkQuantum || chunk_rows % kChunkQuantum != 0) return DA_ERR_SHAPE;
+  plan->chunked = false;
   plan->chunk_rows = chunk_rows;
   plan->head_groups = (int)ceil_div(G, kHeadsPerGroup);
   plan->blocks = G > kHeadsPerBlock ? 2 : 1;
@@ -1861,6 +2575,30 @@ void launch_partial_nb(const Plan& pl, const PartialArgs& a, const WsView& w, hi
   }
 }
 
+// ---- chunk kernels (more than 32 query rows per KV head) --------------------
+template <int DK, int DV, int NW>
+void launch_chunk_nw(ChunkArgs a, int resident, hipStream_t s) {
+  a.nqt = (int)ceil_div(a.R, 32 * NW);
+  // Whole items where the slots don't allow a split.
+  a.unit = a.J >= 3 ? kChunkUnit : (int)(ceil_div(a.n_max, kChunkKeys) * kChunkKeys);
+  const int64_t units = (int64_t)a.B * a.nqt * a.h_kv * ceil_div(a.n_max, a.unit);
+    hipLaunchKernelGGL((chunk_partial_kernel<DK, DV, NW>), dim3((unsigned)std::min<int64_t>(units, resident)),
+                     dim3(64 * NW), 0, s, a);
+}
+
+template <int DK, int DV>
+void launch_chunk(const ChunkArgs& a, int resident, float* out, int32_t* len_bump, hipStream_t s) {
+  if constexpr (DK + DV <= 256) {
+    launch_chunk_nw<DK, DV, 8>(a, resident, s);
+  } else {
+    launch_chunk_nw<DK, DV, 4>(a, resident, s);
+  }
+  const int64_t rows = (int64_t)a.B * a.h_kv * a.R;
+  hipLaunchKernelGGL(chunk_merge_kernel<DV>, dim3((unsigned)ceil_div(rows * (DV / 4), kThreads)),
+                     dim3(kThreads), 0, s, out, a.ws_ml, a.ws_acc, a.nvis, rows, a.J, len_bump,
+                     a.B, a.n_max, a.T);
+}
+
 // Query rows (h_q x T) as the plan's query-head count, or -1 if T is out of
 // range or the product overflows.
 int query_rows(int h_q, int T) {
@@ -1908,6 +2646,25 @@ da_status partial_impl(const float* q, const float* K, const float* V, const flo
                       scale * kLog2e, B, rows, h_kv, n_max, T, direct, bump};
   hipStream_t s = static_cast<hipStream_t>(stream);
   (void)hipGetLastError();
+  if (allow_direct && chunk_rows == 0 && T > 1 && rows / h_kv >= kChunkMinRows) {
+    if (out_plan) out_plan->chunked = true;
+    const ChunkArgs c{q, const_cast<float*>(K), const_cast<float*>(V), k_new, v_new, len,
+                      scale * kLog2e, B, h_kv, n_max, T, rows / h_kv, 0, 0, pl.J, w.nvis, w.ml,
+                      w.acc};
+    float* o = const_cast<float*>(out);
+    int32_t* lb = k_new ? const_cast<int32_t*>(len) : nullptr;
+    const int cus = device_resident();
+    if (d_k == 64 && d_v == 64) launch_chunk<64, 64>(c, cus, o, lb, s);
+    else if (d_k == 64 && d_v == 128) launch_chunk<64, 128>(c, cus, o, lb, s);
+    else if (d_k == 64 && d_v == 256) launch_chunk<64, 256>(c, cus, o, lb, s);
+    else if (d_k == 128 && d_v == 64) launch_chunk<128, 64>(c, cus, o, lb, s);
+    else if (d_k == 128 && d_v == 128) launch_chunk<128, 128>(c, cus, o, lb, s);
+    else if (d_k == 128 && d_v == 256) launch_chunk<128, 256>(c, cus, o, lb, s);
+    else if (d_k == 256 && d_v == 64) launch_chunk<256, 64>(c, cus, o, lb, s);
+    else if (d_k == 256 && d_v == 128) launch_chunk<256, 128>(c, cus, o, lb, s);
+    else launch_chunk<256, 256>(c, cus, o, lb, s);
+    return launch_status();
+  }
   if (d_k == 64 && d_v == 64) launch_partial_nb<64, 64>(pl, a, w, s);
   else if (d_k == 64 && d_v == 128) launch_partial_nb<64, 128>(pl, a, w, s);
   else if (d_k == 64 && d_v == 256) launch_partial_nb<64, 256>(pl, a, w, s);
@@ -2084,7 +2841,8 @@ da_status da_decode_multi_step(const float* q, float* K, float* V, const float* 
   da_status st = partial_impl(q, K, V, k_new, v_new, len, scale, B, h_q, h_kv, n_max, d_k, d_v,
                               T, 0, workspace, workspace_bytes, stream, out, true, &pl, true);
   if (st != DA_OK) return st;
-  if (direct_two_waves(pl, d_k, d_v)) return DA_OK;  // the direct form did the whole step
+  // The chunk kernels or the direct form did the whole step.
+  if (pl.chunked || direct_two_waves(pl, d_k, d_v)) return DA_OK;
   return merge_impl(out, len, B, h_q, h_kv, n_max, d_k, d_v, T, pl.chunk_rows, workspace,
                     workspace_bytes, stream);
 }
@@ -2151,7 +2909,7 @@ da_status da_decode_multi_ex(const float* q, const float* K, const float* V,
                               d_v, T, chunk_rows, workspace, workspace_bytes, stream, out, true,
                               &pl, true);
   if (st != DA_OK) return st;
-  if (pl.single_chunk) return DA_OK;                  // the direct form wrote out
+  if (pl.chunked || pl.single_chunk) return DA_OK;    // the chunk kernels or the direct form
   return merge_impl(out, nullptr, B, h_q, h_kv, n_max, d_k, d_v, T, pl.chunk_rows, workspace,
                     workspace_bytes, stream);
 }
