@@ -125,6 +125,22 @@ constexpr int kDefaultChunkRows = 768;
 // leave the last round's long slabs alone on the chip.)
 constexpr int64_t kDirectMinSlabs = 2048;
 constexpr int kDirectMaxRows = 6 * kChunkQuantum;
+// Workgroups per slab of the two-wave ranges, at most: a slab's visits are
+// merged by one workgroup per head, and beyond this the merge costs more than
+// the shorter ranges give (one slab of 131072 rows, 16 heads: 53 us at 64, 36
+// at 128 and 256, 45 at 512; two of 40000-65000 rows, 8 heads: 36.7, 32.7, 38).
+constexpr int kMaxSlabVisitors = 128;
+// Slabs of a single segment are cut into units all the same where one
+// workgroup per slab would leave most of the chip idle: at most
+// kSplitMaxSlabs slabs of at least kSplitMinFloats values (512 rows at d =
+// 128).  The merge launch costs what the shorter reads save near that line
+// (steps of 32/8 heads, d = 128, direct form / split: 8 slabs x 700 rows 22.3
+// / 17.9 us, 64 x 765 23.8 / 21.1, 64 x 509 18.9 / 17.6, 4 x 381 15.8 / 17.6,
+// 128 x 765 24.7 / 28.9; 8 slabs x 700 rows at d = 256 44.5 / 20.4).
+constexpr int kSplitMaxSlabs = 64;
+constexpr int64_t kSplitMinFloats = 131072;
+// The workspace that the library holds itself (da_decode_attn_noalloc).
+constexpr size_t kScratchBytes = size_t(64) << 20;
 // Visit slots per slab for dynamic visits, in units of the even share of
 // resident workgroups per slab.
 constexpr int kVisitSlack = 4;
@@ -1576,8 +1592,20 @@ __global__ __launch_bounds__(kThreads) void decode_merge_kernel(
     m = mn;
   };
   if (pv < nv) add(st0, a0);
-  for (int jj = pv + kLanesV; jj < nv; jj += kLanesV)
-    add(ml[jj], load4(acc + (int64_t)jj * DV + 4 * ch));
+  // The rest four at a time, so that their loads share a round trip.
+  int jj = pv + kLanesV;
+  for (; jj + 3 * kLanesV < nv; jj += 4 * kLanesV) {
+    float2 st[4];
+    f4 a[4];
+#pragma unroll
+    for (int x = 0; x < 4; ++x) {
+      st[x] = ml[jj + x * kLanesV];
+      a[x] = load4(acc + (int64_t)(jj + x * kLanesV) * DV + 4 * ch);
+    }
+#pragma unroll
+    for (int x = 0; x < 4; ++x) add(st[x], a[x]);
+  }
+  for (; jj < nv; jj += kLanesV) add(ml[jj], load4(acc + (int64_t)jj * DV + 4 * ch));
   __shared__ float sh_m[kThreads], sh_l[kThreads];
   __shared__ f4 sh_o[kThreads];
   sh_m[tid] = m;
@@ -2399,9 +2427,11 @@ int dynamic_min_units() {
 
 // The work decomposition for these shapes with `resident` resident
 // workgroups.  Every size below grows with `resident`, so the plan for
-// kMaxResident bounds the workspace of any device's plan.
-da_status make_plan(int B, int h_q, int h_kv, int n_max, int d_k, int d_v, int chunk_rows,
-                    int resident, Plan* plan) {
+// kMaxResident bounds the workspace of any device's plan.  A fine plan cuts
+// small batches into scheduling units instead of chunks, and short slabs that
+// are too few to fill the chip as well (make_plan decides).
+da_status plan_for(int B, int h_q, int h_kv, int n_max, int d_k, int d_v, int chunk_rows,
+                   int resident, bool fine, Plan* plan) {
   da_status st = check_shapes(B, h_q, h_kv, n_max, d_k, d_v);
   if (st != DA_OK) return st;
   const int G = h_q / h_kv;
@@ -2424,9 +2454,20 @@ da_status make_plan(int B, int h_q, int h_kv, int n_max, int d_k, int d_v, int c
   plan->slabs = B * h_kv * plan->head_groups;
   plan->merge_heads = std::min(G, plan->blocks * kHeadsPerBlock);
   const int64_t chunks_per_slab = ceil_div(n_max, chunk_rows);
-  plan->single_chunk = chunks_per_slab == 1;
-  // One resident workgroup per CU, fewer if there are fewer chunks than that.
-  plan->grid = (int)std::max<int64_t>(1, std::min<int64_t>(resident, chunks_per_slab * plan->slabs));
+  plan->single_chunk =
+      chunks_per_slab == 1 && !(fine && B <= kMaxStaticSeqs && plan->slabs <= kSplitMaxSlabs &&
+                                (int64_t)n_max * (d_k + d_v) >= kSplitMinFloats);
+  // One resident workgroup per CU, fewer if there are fewer units of work
+  // than that: scheduling units in a fine plan's static share, else chunks.
+  // (A small batch in chunks of 768 rows left most of the chip idle: one
+  // sequence of 2900 rows, 32/8 heads, d = 128 23.2 us in chunks, 17.0 in
+  // units; 2 sequences of 3000-8000 rows, 8/2 heads, d = 256 44.2 and 30.3;
+  // MQA 32/1 heads, 16000 rows 43.4 and 28.6.)
+  const bool can_static = !plan->single_chunk && B <= kMaxStaticSeqs;
+  const int64_t units =
+      (int64_t)plan->slabs * ceil_div(n_max, ring_tiles(plan->blocks, d_k, d_v) * kWaves * kTileRows);
+  plan->grid = (int)std::max<int64_t>(
+      1, std::min<int64_t>(resident, fine && can_static ? units : chunks_per_slab * plan->slabs));
   // Static share: off for single-chunk caches (direct form) and for batches
   // whose per-workgroup prefix over sequences would be long.  With two or
   // more slabs per workgroup (one column block) the even split of whole
@@ -2434,11 +2475,9 @@ da_status make_plan(int B, int h_q, int h_kv, int n_max, int d_k, int d_v, int c
   // slabs are saved (with two column blocks and many slabs the dynamic
   // remainders measured 0-1.5 % faster); with few units per workgroup the
   // dynamic share cannot move work (kDynamicMinUnits).
-  const int64_t units =
-      (int64_t)plan->slabs * ceil_div(n_max, ring_tiles(plan->blocks, d_k, d_v) * kWaves * kTileRows);
   const bool few = units < (int64_t)dynamic_min_units() * plan->grid;
   plan->fnum = 0;
-  if (!plan->single_chunk && B <= kMaxStaticSeqs)
+  if (can_static)
     plan->fnum = (plan->blocks == 1 && (int64_t)plan->slabs >= 2 * (int64_t)plan->grid) || few
                      ? kStaticDen : kStaticNum;
   // Slabs of at most kDirectMaxRows rows (one column block, d_k + d_v <=
@@ -2452,12 +2491,16 @@ da_status make_plan(int B, int h_q, int h_kv, int n_max, int d_k, int d_v, int c
   // CU count, so that the workspace sized for the largest grid covers every
   // device.)  Longer slabs take the same form when the whole batch is short
   // (kTwoWaveMaxUnits) and the static plan applies.
-  const bool tw_base = !plan->single_chunk && B <= kMaxStaticSeqs && plan->blocks == 1 &&
-                       d_k + d_v <= 256;
+  const bool tw_base = can_static && plan->blocks == 1 && d_k + d_v <= 256;
+  // Its workgroups: two per CU, fewer if there are fewer units (128 rows).
+  const int64_t per_slab =
+      fine ? std::min<int64_t>(kMaxSlabVisitors, ceil_div(n_max, 2 * kWaves * kTileRows))
+           : chunks_per_slab;
+  const int64_t two_wave_grid = std::min<int64_t>(2 * (int64_t)resident, per_slab * plan->slabs);
   const bool tw_short_batch = units < (int64_t)kTwoWaveMaxUnits * kMaxResident;
   plan->two_waves = tw_base && (n_max <= kDirectMaxRows || (tw_short_batch && few));
   if (plan->two_waves) {
-    plan->grid = (int)std::min<int64_t>(2 * (int64_t)resident, chunks_per_slab * plan->slabs);
+    plan->grid = (int)two_wave_grid;
     plan->fnum = kStaticDen;
   }
   // Scheduling units (static ranges and dynamic hand-outs) are one ring turn
@@ -2478,7 +2521,7 @@ da_status make_plan(int B, int h_q, int h_kv, int n_max, int d_k, int d_v, int c
     // The slots of the two-wave form, which the same shapes take under
     // another DECODE_ATTN_DYNAMIC_MIN_UNITS: the workspace a caller sizes
     // must not depend on the environment.
-    const int64_t g2 = std::min<int64_t>(2 * (int64_t)resident, chunks_per_slab * plan->slabs);
+    const int64_t g2 = two_wave_grid;
     const int64_t r2 = 2 * kWaves * kTileRows;
     const int64_t J2 = std::min<int64_t>(g2, ceil_div(n_max, r2)) + 1 +
                        std::max<int64_t>(1, std::min(ceil_div(n_max, r2),
@@ -2493,6 +2536,23 @@ da_status make_plan(int B, int h_q, int h_kv, int n_max, int d_k, int d_v, int c
   plan->ml_bytes = pad256(slots * sizeof(float2));
   plan->bytes = plan->counter_bytes + plan->ml_bytes + slots * (size_t)d_v * sizeof(float);
   return DA_OK;
+}
+
+// The plan: fine unless the caller chose the segment size, or its partials
+// would take more than the workspace that the library holds itself (so that
+// the shapes that fit there stay the same).  Decided for the largest grid, so
+// that every device decides alike.
+da_status make_plan(int B, int h_q, int h_kv, int n_max, int d_k, int d_v, int chunk_rows,
+                    int resident, Plan* plan) {
+  bool fine = chunk_rows == 0;
+  if (fine) {
+    const da_status st =
+        plan_for(B, h_q, h_kv, n_max, d_k, d_v, 0, kMaxResident, true, plan);
+    if (st != DA_OK) return st;
+    fine = plan->bytes <= kScratchBytes;
+    if (fine && resident == kMaxResident) return st;
+  }
+  return plan_for(B, h_q, h_kv, n_max, d_k, d_v, chunk_rows, resident, fine, plan);
 }
 
 struct WsView {
@@ -2737,7 +2797,6 @@ da_status clear_words(void* p, size_t bytes, hipStream_t s) {
 // memory: its device address is looked up per device (hipGetSymbolAddress)
 // and only that address is passed to kernels.
 // ---------------------------------------------------------------------------
-static constexpr size_t kScratchBytes = size_t(64) << 20;
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 
 static std::atomic<void*> g_scratch_ptr[kMaxDevices];
@@ -2843,7 +2902,7 @@ da_status da_decode_multi_step(const float* q, float* K, float* V, const float* 
   if (st != DA_OK) return st;
   // The chunk kernels or the direct form did the whole step.
   if (pl.chunked || direct_two_waves(pl, d_k, d_v)) return DA_OK;
-  return merge_impl(out, len, B, h_q, h_kv, n_max, d_k, d_v, T, pl.chunk_rows, workspace,
+  return merge_impl(out, len, B, h_q, h_kv, n_max, d_k, d_v, T, 0, workspace,
                     workspace_bytes, stream);
 }
 
@@ -2910,7 +2969,7 @@ da_status da_decode_multi_ex(const float* q, const float* K, const float* V,
                               &pl, true);
   if (st != DA_OK) return st;
   if (pl.chunked || pl.single_chunk) return DA_OK;    // the chunk kernels or the direct form
-  return merge_impl(out, nullptr, B, h_q, h_kv, n_max, d_k, d_v, T, pl.chunk_rows, workspace,
+  return merge_impl(out, nullptr, B, h_q, h_kv, n_max, d_k, d_v, T, chunk_rows, workspace,
                     workspace_bytes, stream);
 }
 
