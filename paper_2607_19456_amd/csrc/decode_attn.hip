@@ -2425,13 +2425,20 @@ int dynamic_min_units() {
   return (*end == 0 && v >= 0 && v <= (1L << 20)) ? (int)v : kDynamicMinUnits;
 }
 
+void size_plan(int B, int h_q, int d_v, Plan* plan) {
+  const size_t heads = (size_t)B * h_q;
+  const size_t slots = heads * plan->J;
+  plan->line_bytes = pad256((size_t)plan->slabs * kCounterStride * sizeof(unsigned));
+  plan->counter_bytes = plan->line_bytes + pad256(heads * sizeof(unsigned));
+  plan->ml_bytes = pad256(slots * sizeof(float2));
+  plan->bytes = plan->counter_bytes + plan->ml_bytes + slots * (size_t)d_v * sizeof(float);
+}
+
 // The work decomposition for these shapes with `resident` resident
 // workgroups.  Every size below grows with `resident`, so the plan for
-// kMaxResident bounds the workspace of any device's plan.  A fine plan cuts
-// small batches into scheduling units instead of chunks, and short slabs that
-// are too few to fill the chip as well (make_plan decides).
-da_status plan_for(int B, int h_q, int h_kv, int n_max, int d_k, int d_v, int chunk_rows,
-                   int resident, bool fine, Plan* plan) {
+// kMaxResident bounds the workspace of any device's plan.
+da_status plan_chunks(int B, int h_q, int h_kv, int n_max, int d_k, int d_v, int chunk_rows,
+                      int resident, Plan* plan) {
   da_status st = check_shapes(B, h_q, h_kv, n_max, d_k, d_v);
   if (st != DA_OK) return st;
   const int G = h_q / h_kv;
@@ -2454,20 +2461,14 @@ da_status plan_for(int B, int h_q, int h_kv, int n_max, int d_k, int d_v, int ch
   plan->slabs = B * h_kv * plan->head_groups;
   plan->merge_heads = std::min(G, plan->blocks * kHeadsPerBlock);
   const int64_t chunks_per_slab = ceil_div(n_max, chunk_rows);
-  plan->single_chunk =
-      chunks_per_slab == 1 && !(fine && B <= kMaxStaticSeqs && plan->slabs <= kSplitMaxSlabs &&
-                                (int64_t)n_max * (d_k + d_v) >= kSplitMinFloats);
-  // One resident workgroup per CU, fewer if there are fewer units of work
-  // than that: scheduling units in a fine plan's static share, else chunks.
-  // (A small batch in chunks of 768 rows left most of the chip idle: one
-  // sequence of 2900 rows, 32/8 heads, d = 128 23.2 us in chunks, 17.0 in
-  // units; 2 sequences of 3000-8000 rows, 8/2 heads, d = 256 44.2 and 30.3;
-  // MQA 32/1 heads, 16000 rows 43.4 and 28.6.)
+  plan->single_chunk = chunks_per_slab == 1;
+  // One resident workgroup per CU, fewer if there are fewer chunks than that
+  // (refine_grid raises it for wholly static plans).
   const bool can_static = !plan->single_chunk && B <= kMaxStaticSeqs;
   const int64_t units =
       (int64_t)plan->slabs * ceil_div(n_max, ring_tiles(plan->blocks, d_k, d_v) * kWaves * kTileRows);
   plan->grid = (int)std::max<int64_t>(
-      1, std::min<int64_t>(resident, fine && can_static ? units : chunks_per_slab * plan->slabs));
+      1, std::min<int64_t>(resident, chunks_per_slab * plan->slabs));
   // Static share: off for single-chunk caches (direct form) and for batches
   // whose per-workgroup prefix over sequences would be long.  With two or
   // more slabs per workgroup (one column block) the even split of whole
@@ -2492,11 +2493,8 @@ da_status plan_for(int B, int h_q, int h_kv, int n_max, int d_k, int d_v, int ch
   // device.)  Longer slabs take the same form when the whole batch is short
   // (kTwoWaveMaxUnits) and the static plan applies.
   const bool tw_base = can_static && plan->blocks == 1 && d_k + d_v <= 256;
-  // Its workgroups: two per CU, fewer if there are fewer units (128 rows).
-  const int64_t per_slab =
-      fine ? std::min<int64_t>(kMaxSlabVisitors, ceil_div(n_max, 2 * kWaves * kTileRows))
-           : chunks_per_slab;
-  const int64_t two_wave_grid = std::min<int64_t>(2 * (int64_t)resident, per_slab * plan->slabs);
+  const int64_t two_wave_grid =
+      std::min<int64_t>(2 * (int64_t)resident, chunks_per_slab * plan->slabs);
   const bool tw_short_batch = units < (int64_t)kTwoWaveMaxUnits * kMaxResident;
   plan->two_waves = tw_base && (n_max <= kDirectMaxRows || (tw_short_batch && few));
   if (plan->two_waves) {
@@ -2529,30 +2527,49 @@ da_status plan_for(int B, int h_q, int h_kv, int n_max, int d_k, int d_v, int ch
     J = std::max(J, J2);
   }
   plan->J = (int)J;
-  const size_t heads = (size_t)B * h_q;
-  const size_t slots = heads * plan->J;
-  plan->line_bytes = pad256((size_t)plan->slabs * kCounterStride * sizeof(unsigned));
-  plan->counter_bytes = plan->line_bytes + pad256(heads * sizeof(unsigned));
-  plan->ml_bytes = pad256(slots * sizeof(float2));
-  plan->bytes = plan->counter_bytes + plan->ml_bytes + slots * (size_t)d_v * sizeof(float);
+  size_plan(B, h_q, d_v, plan);
   return DA_OK;
 }
 
-// The plan: fine unless the caller chose the segment size, or its partials
-// would take more than the workspace that the library holds itself (so that
-// the shapes that fit there stay the same).  Decided for the largest grid, so
-// that every device decides alike.
+// A wholly static plan's workgroups: as many as there are units, instead of
+// chunks -- a small batch in chunks of 768 rows leaves most of the chip idle
+// (one sequence of 2900 rows, 32/8 heads, d = 128: 23.2 us in chunks, 17.0 in
+// units; 2 sequences of 3000-8000 rows, 8/2 heads, d = 256 44.2 and 30.3; MQA
+// 32/1 heads, 16000 rows 43.4 and 28.6) -- but at most kMaxSlabVisitors per
+// slab at two per CU, and no more than the plan's slots hold whatever the
+// lengths: all of them may visit one slab.
+void refine_grid(int n_max, int resident, Plan* plan) {
+  const int64_t per_slab = ceil_div(n_max, plan->dyn_rows);
+  int64_t grid = plan->two_waves
+                     ? std::min<int64_t>(2 * (int64_t)resident,
+                                         plan->slabs * std::min<int64_t>(kMaxSlabVisitors, per_slab))
+                     : std::min<int64_t>(resident, plan->slabs * per_slab);
+  if (per_slab + 1 > plan->J) grid = std::min<int64_t>(grid, std::max(plan->grid, plan->J - 1));
+  plan->grid = (int)std::max<int64_t>(1, grid);
+}
+
 da_status make_plan(int B, int h_q, int h_kv, int n_max, int d_k, int d_v, int chunk_rows,
                     int resident, Plan* plan) {
-  bool fine = chunk_rows == 0;
-  if (fine) {
-    const da_status st =
-        plan_for(B, h_q, h_kv, n_max, d_k, d_v, 0, kMaxResident, true, plan);
-    if (st != DA_OK) return st;
-    fine = plan->bytes <= kScratchBytes;
-    if (fine && resident == kMaxResident) return st;
+  const da_status st = plan_chunks(B, h_q, h_kv, n_max, d_k, d_v, chunk_rows, resident, plan);
+  if (st != DA_OK || chunk_rows != 0 || B > kMaxStaticSeqs) return st;
+  if (!plan->single_chunk) {
+    if (plan->fnum == kStaticDen) refine_grid(n_max, resident, plan);
+  } else if (plan->slabs <= kSplitMaxSlabs && (int64_t)n_max * (d_k + d_v) >= kSplitMinFloats) {
+    // A slot for every unit; the library's own workspace goes on holding what
+    // it held.
+    Plan split = *plan;
+    split.single_chunk = false;
+    split.two_waves = plan->blocks == 1 && d_k + d_v <= 256;
+    split.fnum = kStaticDen;
+    split.dyn_rows =
+        (split.two_waves ? 2 : ring_tiles(plan->blocks, d_k, d_v)) * kWaves * kTileRows;
+    split.Jd = 1;
+    split.J = (int)ceil_div(n_max, split.dyn_rows) + 1;
+    refine_grid(n_max, resident, &split);
+    size_plan(B, h_q, d_v, &split);
+    if (split.bytes <= kScratchBytes) *plan = split;
   }
-  return plan_for(B, h_q, h_kv, n_max, d_k, d_v, chunk_rows, resident, fine, plan);
+  return DA_OK;
 }
 
 struct WsView {
