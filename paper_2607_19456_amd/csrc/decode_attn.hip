@@ -860,20 +860,27 @@ __device__ __forceinline__ int64_t wave_incl_scan(int64_t v, int lane) {
 }
 
 // Wave-wide (all 64 lanes).  Static units of one slab of sequence `bq` and
-// of one slab of each sequence before it; returns the static units of one
-// slab summed over all sequences.
+// of one slab of each sequence before it (bq < 0: *st_bq = the most that any
+// slab has); returns the static units of one slab summed over all sequences.
 __device__ int64_t static_scan(const int32_t* __restrict__ len, int B, int n_max, bool app, int T,
                                int Cd, int fnum, int bq, int lane, int64_t* before, int* st_bq) {
   int64_t carry = 0;
+  int most = 0;
   for (int b0 = 0; b0 < B; b0 += kWave) {
     const int b = b0 + lane;
     const int64_t v = b < B ? static_units(decode_rows(len[b], n_max, app, T), Cd, fnum) : 0;
+    most = max(most, (int)v);
     const int64_t incl = wave_incl_scan(v, lane);
     if (bq >= b0 && bq < b0 + kWave) {
       *before = carry + __shfl(incl - v, bq - b0);
       *st_bq = (int)__shfl(v, bq - b0);
     }
     carry += __shfl(incl, kWave - 1);
+  }
+  if (bq < 0) {
+#pragma unroll
+    for (int d = 1; d < kWave; d <<= 1) most = max(most, __shfl_xor(most, d));
+    *st_bq = most;
   }
   return carry;
 }
@@ -1054,7 +1061,7 @@ __global__ __launch_bounds__(kThreads, W) void decode_partial_kernel(
   // rows itself -- no merge, and no other workgroup touches its counter line.
   bool first = true;
   // This workgroup's static range, units [u_lo, u_hi) of Ru (wave 0 only).
-  const int Gw = (int)gridDim.x;
+  int Gw = (int)gridDim.x;
   const int rank = (int)blockIdx.x;
   int64_t Ru = 0, u_lo = 0, u_hi = 0;
   int ws_s = -1, ws_st = 0;         // slab and units per slab of the last static visit
@@ -1062,8 +1069,15 @@ __global__ __launch_bounds__(kThreads, W) void decode_partial_kernel(
     int64_t before;
     int st;
     Ru = (int64_t)per_b * static_scan(len, B, n_max, app, T, Cd, fnum, -1, lane, &before, &st);
-    u_lo = (int64_t)rank * Ru / Gw;
-    u_hi = (int64_t)(rank + 1) * Ru / Gw;
+    // As many workgroups take part as keep every slab's visits within its J
+    // slots: a slab of st units meets at most floor((st - 1) / (Ru / Gw)) + 2
+    // ranges.
+    if (fnum >= kStaticDen && st > J)
+      Gw = (int)std::max<int64_t>(1, std::min<int64_t>(Gw, Ru * (J - 2) / st));
+    if (rank < Gw) {
+      u_lo = (int64_t)rank * Ru / Gw;
+      u_hi = (int64_t)(rank + 1) * Ru / Gw;
+    }
   }
 
   while (true) {
@@ -1380,7 +1394,8 @@ __global__ __launch_bounds__(kThreads, W) void decode_partial_kernel(
           for (int p = 0; p < R; ++p) {
             const int r = row_of(t + p);
             load(ring[(p + R - 1) % R], row_of(t + p + R - 1), last_row);
-            if (r <= last_row) {
+            // (Only a visit's last segment may end inside a turn.)
+            if (r <= last_row && (p == 0 || t + p < ctpw)) {
               if constexpr (PAIRS)
                 process_tile_pairs<DK, DV, NB, CAUSAL, kPin>(ring[p], r, lim, src, lane,
                                                              sh_k[PAIRS ? wave : 0], sh_q, qr,
@@ -2502,7 +2517,8 @@ da_status plan_chunks(int B, int h_q, int h_kv, int n_max, int d_k, int d_v, int
     plan->fnum = kStaticDen;
   }
   // Scheduling units (static ranges and dynamic hand-outs) are one ring turn
-  // of the four waves when there is a static share, else whole chunks.
+  // of the four waves when there is a static share, else whole chunks
+  // (refine_grid makes some wholly static plans' smaller).
   const int ring = plan->two_waves ? 2 : ring_tiles(plan->blocks, d_k, d_v);
   plan->dyn_rows = plan->fnum > 0 ? ring * kWaves * kTileRows : chunk_rows;
   // Static slots: at most one per static unit of a slab plus one, and never
@@ -2531,21 +2547,32 @@ da_status plan_chunks(int B, int h_q, int h_kv, int n_max, int d_k, int d_v, int
   return DA_OK;
 }
 
-// A wholly static plan's workgroups: as many as there are units, instead of
-// chunks -- a small batch in chunks of 768 rows leaves most of the chip idle
-// (one sequence of 2900 rows, 32/8 heads, d = 128: 23.2 us in chunks, 17.0 in
-// units; 2 sequences of 3000-8000 rows, 8/2 heads, d = 256 44.2 and 30.3; MQA
-// 32/1 heads, 16000 rows 43.4 and 28.6) -- but at most kMaxSlabVisitors per
-// slab at two per CU, and no more than the plan's slots hold whatever the
-// lengths: all of them may visit one slab.
+// A wholly static plan's workgroups: one for every kMinRangeRows rows, instead
+// of one for every chunk -- a small batch in chunks of 768 rows leaves most of
+// the chip idle (one sequence of 2900 rows, 32/8 heads, d = 128: 23.2 us in
+// chunks, 17.0 in units; 2 sequences of 3000-8000 rows, 8/2 heads, d = 256
+// 44.2 and 30.3; MQA 32/1 heads, 16000 rows 43.4 and 28.6) -- but at most
+// kMaxSlabVisitors per slab at two per CU.
+constexpr int kMinRangeRows = 128;
 void refine_grid(int n_max, int resident, Plan* plan) {
-  const int64_t per_slab = ceil_div(n_max, plan->dyn_rows);
-  int64_t grid = plan->two_waves
-                     ? std::min<int64_t>(2 * (int64_t)resident,
-                                         plan->slabs * std::min<int64_t>(kMaxSlabVisitors, per_slab))
-                     : std::min<int64_t>(resident, plan->slabs * per_slab);
-  if (per_slab + 1 > plan->J) grid = std::min<int64_t>(grid, std::max(plan->grid, plan->J - 1));
+  const int64_t per_slab = ceil_div(n_max, kMinRangeRows);
+  const int64_t grid =
+      plan->two_waves ? std::min<int64_t>(2 * (int64_t)resident,
+                                          plan->slabs * std::min<int64_t>(kMaxSlabVisitors, per_slab))
+                      : std::min<int64_t>(resident, plan->slabs * per_slab);
   plan->grid = (int)std::max<int64_t>(1, grid);
+  // Its units: single tiles of the four waves (64 rows) instead of ring turns
+  // where turns are long against a workgroup's share -- the four-tile turns of
+  // two column blocks (MQA, 64 sequences of 512-8192 rows 78.0 -> 74.5 us; 2 x
+  // 600 rows 25.6 -> 21.3) and the two-wave form from two turns per workgroup
+  // on (16 ragged sequences of 200-4000 rows, 32/8 heads 50.7 -> 50.0; four
+  // rows a step, 8 sequences 42.1 -> 40.9).  A visit that ends inside a turn
+  // pays for all of it: one turn or less per workgroup (one sequence of 2900
+  // rows 17.4 and 18.1) and the two-tile turns of one column block at one per
+  // CU (d = 256, 4 sequences 79.5 and 82.0) keep turns.
+  const bool turns_long = plan->blocks == 2 && plan->dyn_rows == 4 * kWaves * kTileRows;
+  const bool turns_many = plan->two_waves && plan->slabs * per_slab >= 2 * (int64_t)plan->grid;
+  if (turns_long || turns_many) plan->dyn_rows = kWaves * kTileRows;
 }
 
 da_status make_plan(int B, int h_q, int h_kv, int n_max, int d_k, int d_v, int chunk_rows,
@@ -2555,8 +2582,8 @@ da_status make_plan(int B, int h_q, int h_kv, int n_max, int d_k, int d_v, int c
   if (!plan->single_chunk) {
     if (plan->fnum == kStaticDen) refine_grid(n_max, resident, plan);
   } else if (plan->slabs <= kSplitMaxSlabs && (int64_t)n_max * (d_k + d_v) >= kSplitMinFloats) {
-    // A slot for every unit; the library's own workspace goes on holding what
-    // it held.
+    // A slot for every kMinRangeRows rows; the library's own workspace goes on
+    // holding what it held.
     Plan split = *plan;
     split.single_chunk = false;
     split.two_waves = plan->blocks == 1 && d_k + d_v <= 256;
@@ -2564,7 +2591,7 @@ da_status make_plan(int B, int h_q, int h_kv, int n_max, int d_k, int d_v, int c
     split.dyn_rows =
         (split.two_waves ? 2 : ring_tiles(plan->blocks, d_k, d_v)) * kWaves * kTileRows;
     split.Jd = 1;
-    split.J = (int)ceil_div(n_max, split.dyn_rows) + 1;
+    split.J = (int)ceil_div(n_max, kMinRangeRows) + 2;
     refine_grid(n_max, resident, &split);
     size_plan(B, h_q, d_v, &split);
     if (split.bytes <= kScratchBytes) *plan = split;

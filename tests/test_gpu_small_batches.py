@@ -21,6 +21,11 @@ SHAPES = [
     (1, 8, 1, 64, 64, 16384, [16383]),           # as many visitors as a slab may have
     (1, 8, 1, 64, 64, 16513, [16512]),           # more units than that
     (3, 2, 1, 64, 64, 2000, [0, 0, 1]),          # almost nothing to do
+    # Units of single tiles, more of them in one slab than it has slots: fewer
+    # workgroups take part.
+    (16, 8, 8, 64, 64, 4096, [4095] + [0] * 15),
+    (8, 32, 1, 64, 64, 8192, [0] * 7 + [8190]),
+    (8, 32, 1, 64, 64, 2049, [2048, 64, 65, 63, 0, 1, 2000, 1030]),    # visits end inside turns
 ]
 
 
