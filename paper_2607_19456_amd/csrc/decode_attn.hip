@@ -1689,13 +1689,13 @@ __global__ __launch_bounds__(kThreads) void decode_merge_kernel(
 // the visit is then formed again in plain fp32.
 //
 // Matrix-bound: 2 sequences x 32/8 heads x 512 rows behind 1000-7600 keys, d =
-// 128 (86 GFLOP; 105 us at the 16-bit rate with three products for one): 300
+// 128 (86 GFLOP; 105 us at the 16-bit rate with three products for one): 296
 // us, with the fp32 products in groups of 32 rows 940 us.  Prompt of 1500
-// rows x 16 heads, d = 64: 67 us from 237.  Of a tile's 6300 cycles per SIMD
+// rows x 16 heads, d = 64: 64 us from 237.  Of a tile's 6000 cycles per SIMD
 // (two waves) 3072 are matrix work; the rest is the waves' softmax and staging
 // where it finds no partner.  Few rows gain too (8 sequences x 64/8 heads x 8
 // rows behind 2000-8000 keys 119 -> 93 us; 5 rows behind 20000-32000 293 ->
-// 232), since a tile is read and staged once for all of a KV head's rows; a
+// 222), since a tile is read and staged once for all of a KV head's rows; a
 // single row per head (T = 1) with more than 32 heads per KV head does not (8
 // x 64/1 heads behind 9000-16000 keys: 54 us with two groups of 32, 69 here)
 // and keeps the groups of 32.
@@ -1715,8 +1715,11 @@ typedef float f16v __attribute__((ext_vector_type(16)));
 
 constexpr int kChunkKeys = 32;          // keys per staged tile
 constexpr int kChunkMinRows = 33;       // query rows per KV head from which the chunk kernels run
-// Keys per scheduling unit of a query tile.
-constexpr int kChunkUnit = 128;
+// Keys per scheduling unit of a query tile: a visit costs about 15 us beside
+// its tiles, finer units even out more (1500 rows of an empty cache, 16 heads,
+// d = 64: 65.8 us at 32, 64.3 at 64, 66.9 at 128, 73.5 at 256; 300 rows, 32/8
+// heads, d = 128: 45.6, 33.8, 35.8, 43.2).
+constexpr int kChunkUnit = 64;
 constexpr float kChunkLift = 128.f;     // weights are staged times this
 
 // Eight fp32 values times a power of two as the fp16 sum h + l.  (Packed
@@ -1844,12 +1847,9 @@ void chunk_partial_kernel(const ChunkArgs a) {
   constexpr int kKPiece = 16 * (kChunkKeys + 1);        // bytes between K pieces
   constexpr int kKPlane = KC * kKPiece;
   constexpr int kVPlane = 64 * DV;
-  // K of the current and the next tile; V of the previous one as well where
-  // waves update late (see `early`).
-  constexpr int kVBufs = NW == 8 ? 3 : 2;
   __shared__ __align__(16) char sh_k[2][2 * kKPlane];
-  __shared__ __align__(16) char sh_v[kVBufs][2 * kVPlane];
-  __shared__ int sh_need[2][2];                         // largest exponent of K, V staged
+  __shared__ __align__(16) char sh_v[2][2 * kVPlane];
+  __shared__ __align__(8) int sh_need[2][2];            // largest exponent of K, V staged
   __shared__ int sh_bad;
 
   const int tid = threadIdx.x;
@@ -1973,28 +1973,36 @@ void chunk_partial_kernel(const ChunkArgs a) {
       if constexpr (KU % NT == 0 && UN % NT == 0) return y >= KU / NT;
       else return !unit_k(y) && y * NT + wave * 64 < UN;
     };
+    // Where this lane's units start, from the tile's first row of K or V.
+    unsigned roff[UPT];
+#pragma unroll
+    for (int y = 0; y < UPT; ++y) {
+      const int uw = y * NT + wave * 64;
+      const int kg = (uw - KU) / DV;
+      roff[y] = unit_k(y) ? (uw / KC + lkey) * DK + 8 * lc
+                          : (16 * (kg >> 1) + 4 * (kg & 1)) * DV + (uw - KU) % DV + lane;
+    }
     auto load_tile_raw = [&](int kt) {
       const bool plain = kt + kChunkKeys <= new_lo;
       if (plain || (kt >= new_lo && kt + kChunkKeys <= new_lo + new_cnt)) {
-        const float* Kb = plain ? Ks + (int64_t)kt * DK : Kn + (int64_t)(kt - new_lo) * DK;
-        const float* Vb = plain ? Vs + (int64_t)kt * DV : Vn + (int64_t)(kt - new_lo) * DV;
+        const int64_t r0 = plain ? kt : kt - new_lo;
+        const float* Kb = (plain ? Ks : Kn) + r0 * DK;
+        const float* Vb = (plain ? Vs : Vn) + r0 * DV;
 #pragma unroll
         for (int y = 0; y < UPT; ++y) {
-          const int uw = y * NT + wave * 64;
           if (unit_k(y)) {
-            const float* p = Kb + (uw / KC) * DK;
-            const f4 v0 = load4(p + (unsigned)(lkey * DK + 8 * lc));
-            const f4 v1 = load4(p + (unsigned)(lkey * DK + 8 * lc + 4));
+            const f4 v0 = load4(Kb + roff[y]), v1 = load4(Kb + roff[y] + 4);
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
               raw[y][e] = v0[e];
               raw[y][4 + e] = v1[e];
             }
           } else if (unit_v(y)) {
-            const int kg = (uw - KU) / DV;
-            const float* p = Vb + (16 * (kg >> 1) + 4 * (kg & 1)) * DV + (uw - KU) % DV;
 #pragma unroll
-            for (int e = 0; e < 8; ++e) raw[y][e] = (p + ((e & 3) + 8 * (e >> 2)) * DV)[(unsigned)lane];
+            for (int e = 0; e < 4; ++e) {
+              raw[y][e] = (Vb + e * DV)[roff[y]];
+              raw[y][4 + e] = (Vb + (8 + e) * DV)[roff[y]];
+            }
           }
         }
         return;
@@ -2032,7 +2040,7 @@ void chunk_partial_kernel(const ChunkArgs a) {
     // ---- raw -> LDS with the visit's exponents xe (K, V).  Notes parts that
     // outgrow them (for the next tile: see the loop) or fall far below.
     int xe[2] = {32, 32};
-    auto stage = [&](int buf, int vbuf) {
+    auto stage = [&](int buf) {
 #pragma unroll
       for (int y = 0; y < UPT; ++y) {
         const int uw = y * NT + wave * 64;
@@ -2049,7 +2057,7 @@ void chunk_partial_kernel(const ChunkArgs a) {
           *reinterpret_cast<h8*>(base) = hi;
           *reinterpret_cast<h8*>(base + kKPlane) = lo;
         } else {
-          char* base = sh_v[vbuf] + 16 * (uw - KU) + 16 * lane;
+          char* base = sh_v[buf] + 16 * (uw - KU) + 16 * lane;
           *reinterpret_cast<h8*>(base) = hi;
           *reinterpret_cast<h8*>(base + kVPlane) = lo;
         }
@@ -2099,7 +2107,7 @@ void chunk_partial_kernel(const ChunkArgs a) {
     __syncthreads();
     xe[0] = __builtin_amdgcn_readfirstlane(sh_need[0][0]);
     xe[1] = __builtin_amdgcn_readfirstlane(sh_need[0][1]);
-    stage(0, 0);
+    stage(0);
     if (key0 + kChunkKeys < key1) load_tile_raw(key0 + kChunkKeys);
     __syncthreads();
 
@@ -2111,7 +2119,7 @@ void chunk_partial_kernel(const ChunkArgs a) {
       for (int r = 0; r < 16; ++r) acc[c][r] = 0.f;
 
     bool odd = false;
-    // O^T += V^T P for the tile in V buffer vbuf; a 32-dim block's share is
+    // O^T += V^T P for the tile in buffer vbuf; a 32-dim block's share is
     // added while the next block's products run.
     h8 ph[2], pl[2];
     auto update = [&](int vbuf) {
@@ -2140,26 +2148,17 @@ void chunk_partial_kernel(const ChunkArgs a) {
       }
       acc[DV / 32 - 1] += o[(DV / 32 - 1) & 1];
     };
-    // The two waves of a SIMD go through a tile half a turn apart, so that
-    // one's softmax and staging (vector work) run beside the other's products:
-    // late waves form scores, weights and update of a tile and stage the next
-    // one; early waves start with the update of the tile before, stage, and
-    // form scores and weights.
-    const bool early = NW == 8 && wave < 4;
-    bool pending = false;                               // early: ph, pl wait for their update
-    int buf = 0, vbuf = 0;
-    auto vnext = [](int x) { return x == kVBufs - 1 ? 0 : x + 1; };
-    for (int kt = key0; kt < key1; kt += kChunkKeys, buf ^= 1, vbuf = vnext(vbuf)) {
-      if (pending) {
-        update(vbuf == 0 ? kVBufs - 1 : vbuf - 1);
-        pending = false;
-      }
+    // (Sending a SIMD's two waves through a tile half a turn apart -- one
+    // updating the tile before while the other forms scores -- took 3-5 %
+    // longer: the matrix unit's order of the waves does that by itself.)
+    int buf = 0;
+    for (int kt = key0; kt < key1; kt += kChunkKeys, buf ^= 1) {
+      const int2 need = *reinterpret_cast<const int2*>(sh_need[buf]);
       // A tile of larger values than its exponent holds: raise that, rescale
       // the sums (V), load and stage the tile again.  (Every wave reads the
       // same numbers: their writers passed the last barrier, the next ones of
       // this parity wait for the next.)
-      const int nk = __builtin_amdgcn_readfirstlane(sh_need[buf][0]);
-      const int nvx = __builtin_amdgcn_readfirstlane(sh_need[buf][1]);
+      const int nk = uniform(need.x), nvx = uniform(need.y);
       if (nk > xe[0] + 3 || nvx > xe[1] + 3) {
         if (nvx > xe[1] + 3) {
           const int d = nvx - xe[1];
@@ -2174,17 +2173,16 @@ void chunk_partial_kernel(const ChunkArgs a) {
         xe[0] = max(xe[0], nk);
         __syncthreads();                                // both read by every wave
         load_tile_raw(kt);
-        stage(buf, vbuf);
+        stage(buf);
         if (kt + kChunkKeys < key1) load_tile_raw(kt + kChunkKeys);
         __syncthreads();
       }
       const float fs = fq * scale_from(xe[0], 11);
       const bool more = kt + kChunkKeys < key1;
       auto stage_next = [&] {
-        stage(buf ^ 1, vnext(vbuf));
+        stage(buf ^ 1);
         if (kt + 2 * kChunkKeys < key1) load_tile_raw(kt + 2 * kChunkKeys);
       };
-      if (early && more) stage_next();
       if (kt <= lim_max) {
         const char* kb = sh_k[buf] + h * kKPiece + 16 * i;
         f16v s;
@@ -2239,14 +2237,11 @@ void chunk_partial_kernel(const ChunkArgs a) {
           split8(p, kChunkLift, ph[t], pl[t]);
         }
         l_run += psum;
-        if (early) pending = true;
-        else update(vbuf);
+        update(buf);
       }
-      if (!early && more) stage_next();
+      if (more) stage_next();
       __syncthreads();
     }
-
-    if (pending) update(vbuf == 0 ? kVBufs - 1 : vbuf - 1);
 
     // ---- the visit's partial.
     float L = sum_over_halves(l_run);
