@@ -39,7 +39,9 @@
  *
  * Precision.  fp32 storage and arithmetic (the paper's 4-byte traffic model),
  * products accumulated in fp32 by the matrix cores, exponentials by the
- * hardware base-2 exponential.  Results agree with an exact evaluation within
+ * hardware base-2 exponential.  Steps of more than 32 query rows per KV head
+ * (T > 1) form each fp32 product from three 16-bit ones of two-term sums;
+ * measured, their error is no larger.  Results agree with an exact evaluation within
  * 1e-5 absolute for N(0,1) inputs; the append is a bit-exact copy.
  */
 #ifndef DECODE_ATTN_H
@@ -143,8 +145,9 @@ da_status da_decode_workspace_reset(void *workspace, size_t workspace_bytes,
  * to move work (fewer than 32 units per workgroup), at one per CU.  When
  * every slab is a single segment (n_max <= 768, or at least 2048 (b, KV
  * head) slabs with n_max <= 4608, h_q / h_kv <= 16 and d_k + d_v <= 256) the
- * decode is a single launch that writes out directly.  Equivalent to
- * da_decode_partial followed by da_decode_merge.
+ * decode is a single launch that writes out directly, unless the slabs are
+ * few and long enough to be split (at most 64, n_max * (d_k + d_v) >=
+ * 131072).  Equivalent to da_decode_partial followed by da_decode_merge.
  *
  * Supported: d_k, d_v in {64, 128, 256}; any B, h_q, h_kv >= 1 with h_kv | h_q.
  * workspace: see above; at least da_decode_workspace_bytes(...) bytes,
@@ -165,8 +168,8 @@ da_status da_decode_attn(const float *q, const float *K, const float *V,
  * multi-step cache -- in two kernel launches instead of three: the partial
  * launch reads the new row of each KV head straight from k_new / v_new (and
  * writes it into the cache meanwhile), and the merge advances len.  When
- * every slab is short (n_max within one segment), h_q / h_kv <= 16 and
- * d_k + d_v <= 256, the whole step is one launch: one workgroup per
+ * every slab is short (n_max within one segment, and not split: see above),
+ * h_q / h_kv <= 16 and d_k + d_v <= 256, the whole step is one launch: one workgroup per
  * (b, KV head, head group) writes its output rows, and the last workgroup of
  * each sequence to finish advances len[b].  Same results, same argument
  * rules as the two calls; k_new [B][h_kv][d_k] and v_new [B][h_kv][d_v] must
@@ -218,7 +221,9 @@ da_status da_decode_merge(float *out, int32_t *len, int B, int h_q, int h_kv,
  * with p < 0 gives 0.  T = 1 is da_decode_attn.
  *     q   float [B][h_q][T][d_k]      out float [B][h_q][T][d_v]
  * The T rows of every query head of a group are scored from the same K/V
- * reads (the kernels treat them as h_q*T query heads), so the workspace is
+ * reads (the kernels treat them as h_q*T query heads; from 33 of them per KV
+ * head on in kernels of their own, which skip what no row of a tile sees), so
+ * the workspace is
  * that of a single-row decode with h_q*T query heads:
  * da_decode_workspace_bytes(B, h_q*T, h_kv, ...) bytes, its counter region
  * da_decode_workspace_counter_bytes(B, h_q*T, h_kv, ...).  T <= 4096.  Other
@@ -272,7 +277,8 @@ da_status da_kv_append(float *K, float *V, const float *k_new,
  * T rows at once: da_kv_append applied T times in order, row r of every
  * (b, g) taken from k_new [B][h_kv][T][d_k] / v_new [B][h_kv][T][d_v].  Rows
  * land at len[b] + r while the cache has room; len[b] advances by the rows
- * written.  1 <= T <= 4096; other rules as da_kv_append.
+ * written.  1 <= T <= 4096; other rules as da_kv_append.  One launch for up to
+ * 4096 16-byte pieces per sequence, two above.
  */
 da_status da_kv_append_rows(float *K, float *V, const float *k_new,
                             const float *v_new, int32_t *len, int B, int h_kv,

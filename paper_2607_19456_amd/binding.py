@@ -89,9 +89,17 @@ def _dev(t: torch.Tensor, name: str, dtype) -> int:
     return t.data_ptr()
 
 
+# torch.cuda.current_stream() builds a Stream object: 2.7 us of a 9.3 us call,
+# where the handle alone takes 0.2 us.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream(stream) -> int:
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return s.cuda_stream
+    if stream is not None:
+        return stream.cuda_stream
+    if _raw_stream is not None:
+        return _raw_stream(torch.cuda.current_device())
+    return torch.cuda.current_stream().cuda_stream
 
 
 def chunk_rows(B, h_q, h_kv, n_max, d_k, d_v) -> int:

@@ -5,6 +5,8 @@
 //   kv_append_kernel       eqs. (6)-(7): bit-exact row copies per KV head,
 //                          then len[b] += rows (Proposition 2's (d_k+d_v)*4
 //                          bytes per row); T rows at once for multi-row steps.
+//                          Many rows: kv_append_copy_kernel over the whole
+//                          chip, then kv_append_len_kernel.
 //   decode_partial_kernel  eqs. (1)-(3) for all query heads of each GQA group
 //                          at once, as per-visit partial states: every KV slab
 //                          is read from HBM once and feeds all heads of its
@@ -17,6 +19,9 @@
 //                          len (the whole step in one launch).
 //   decode_merge_kernel    combines each head's partials into its output row
 //                          and resets the scheduling state.
+//   chunk_partial_kernel   the same pair for steps of more than 32 query rows
+//   chunk_merge_kernel     per KV head (prompt chunks), on 16-bit matrix
+//                          products of two-term sums.
 //
 // Work decomposition of decode_partial_kernel
 //   A resident grid of 256-thread workgroups (4 waves) shares the slabs' rows:
@@ -829,7 +834,7 @@ __device__ __forceinline__ void process_tile(const Tile<DK, DV, NB>& T, int row0
 // Static part of the schedule.
 //
 // Rows are scheduled in units of Cd rows (one turn of the tile ring for all
-// four waves).  Every slab of sequence b holds st(b) = floor(fnum/16 * n_b /
+// four waves; in some wholly static plans one tile of each).  Every slab of sequence b holds st(b) = floor(fnum/16 * n_b /
 // Cd) static units at its start (ceil(n_b / Cd), all of it, for fnum = 16);
 // the rest of its rows is its dynamic part,
 // handed out one unit at a time.  The static units of all slabs, in slab
@@ -2570,6 +2575,10 @@ void refine_grid(int n_max, int resident, Plan* plan) {
   if (turns_long || turns_many) plan->dyn_rows = kWaves * kTileRows;
 }
 
+// The plan of a call: plan_chunks', refined where the library chooses the
+// segment size.  (The partials' layout depends on the slots J alone, which the
+// grid's refinement leaves as they are, so every call with the same shapes and
+// chunk_rows agrees on it.)
 da_status make_plan(int B, int h_q, int h_kv, int n_max, int d_k, int d_v, int chunk_rows,
                     int resident, Plan* plan) {
   const da_status st = plan_chunks(B, h_q, h_kv, n_max, d_k, d_v, chunk_rows, resident, plan);
