@@ -2551,15 +2551,18 @@ da_status plan_chunks(int B, int h_q, int h_kv, int n_max, int d_k, int d_v, int
 // of one for every chunk -- a small batch in chunks of 768 rows leaves most of
 // the chip idle (one sequence of 2900 rows, 32/8 heads, d = 128: 23.2 us in
 // chunks, 17.0 in units; 2 sequences of 3000-8000 rows, 8/2 heads, d = 256
-// 44.2 and 30.3; MQA 32/1 heads, 16000 rows 43.4 and 28.6) -- but at most
-// kMaxSlabVisitors per slab at two per CU.
+// 44.2 and 30.3; MQA 32/1 heads, 16000 rows 43.4 and 28.6) -- but only up to
+// one per CU, and kMaxSlabVisitors per slab, where the chunks ask for fewer:
+// with two per CU a batch of that size merges twice the visits of half the
+// length (8 sequences of 4222-4802 rows, 4/4 heads 34.4 us in chunks, 34.5 at
+// one per CU, 37.9 at two; 6 of 3000-6000, 16/4 heads 29.3, 28.4, 31.5).
 constexpr int kMinRangeRows = 128;
-void refine_grid(int n_max, int resident, Plan* plan) {
+void refine_grid(int n_max, int d_k, int d_v, int resident, Plan* plan) {
   const int64_t per_slab = ceil_div(n_max, kMinRangeRows);
-  const int64_t grid =
-      plan->two_waves ? std::min<int64_t>(2 * (int64_t)resident,
-                                          plan->slabs * std::min<int64_t>(kMaxSlabVisitors, per_slab))
-                      : std::min<int64_t>(resident, plan->slabs * per_slab);
+  int64_t grid = std::min<int64_t>(resident, plan->slabs * per_slab);
+  if (plan->two_waves)
+    grid = std::max<int64_t>(plan->grid,
+                             std::min<int64_t>(grid, plan->slabs * (int64_t)kMaxSlabVisitors));
   plan->grid = (int)std::max<int64_t>(1, grid);
   // Its units: single tiles of the four waves (64 rows) instead of ring turns
   // where turns are long against a workgroup's share -- the four-tile turns of
@@ -2568,10 +2571,12 @@ void refine_grid(int n_max, int resident, Plan* plan) {
   // on (16 ragged sequences of 200-4000 rows, 32/8 heads 50.7 -> 50.0; four
   // rows a step, 8 sequences 42.1 -> 40.9).  A visit that ends inside a turn
   // pays for all of it: one turn or less per workgroup (one sequence of 2900
-  // rows 17.4 and 18.1) and the two-tile turns of one column block at one per
-  // CU (d = 256, 4 sequences 79.5 and 82.0) keep turns.
+  // rows 17.4 and 18.1), heads of 64 (30 sequences of 3000 rows 69.6 and 70.5)
+  // and the two-tile turns of one column block at one per CU (d = 256, 4
+  // sequences 79.5 and 82.0) keep turns.
   const bool turns_long = plan->blocks == 2 && plan->dyn_rows == 4 * kWaves * kTileRows;
-  const bool turns_many = plan->two_waves && plan->slabs * per_slab >= 2 * (int64_t)plan->grid;
+  const bool turns_many = plan->two_waves && d_k + d_v > 128 &&
+                          plan->slabs * per_slab >= 2 * (int64_t)plan->grid;
   if (turns_long || turns_many) plan->dyn_rows = kWaves * kTileRows;
 }
 
@@ -2584,7 +2589,7 @@ da_status make_plan(int B, int h_q, int h_kv, int n_max, int d_k, int d_v, int c
   const da_status st = plan_chunks(B, h_q, h_kv, n_max, d_k, d_v, chunk_rows, resident, plan);
   if (st != DA_OK || chunk_rows != 0 || B > kMaxStaticSeqs) return st;
   if (!plan->single_chunk) {
-    if (plan->fnum == kStaticDen) refine_grid(n_max, resident, plan);
+    if (plan->fnum == kStaticDen) refine_grid(n_max, d_k, d_v, resident, plan);
   } else if (plan->slabs <= kSplitMaxSlabs && (int64_t)n_max * (d_k + d_v) >= kSplitMinFloats) {
     // A slot for every kMinRangeRows rows; the library's own workspace goes on
     // holding what it held.
@@ -2596,7 +2601,7 @@ da_status make_plan(int B, int h_q, int h_kv, int n_max, int d_k, int d_v, int c
         (split.two_waves ? 2 : ring_tiles(plan->blocks, d_k, d_v)) * kWaves * kTileRows;
     split.Jd = 1;
     split.J = (int)ceil_div(n_max, kMinRangeRows) + 2;
-    refine_grid(n_max, resident, &split);
+    refine_grid(n_max, d_k, d_v, resident, &split);
     size_plan(B, h_q, d_v, &split);
     if (split.bytes <= kScratchBytes) *plan = split;
   }
