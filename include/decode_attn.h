@@ -40,9 +40,11 @@
  * Precision.  fp32 storage and arithmetic (the paper's 4-byte traffic model),
  * products accumulated in fp32 by the matrix cores, exponentials by the
  * hardware base-2 exponential.  Steps of more than 32 query rows per KV head
- * (T > 1) form each fp32 product from three 16-bit ones of two-term sums;
- * measured, their error is no larger.  Results agree with an exact evaluation within
- * 1e-5 absolute for N(0,1) inputs; the append is a bit-exact copy.
+ * (T > 1) may form each fp32 product from six 16-bit ones of three-term sums,
+ * which hold every bit of an fp32 value whatever stands beside it; what is
+ * left out is at most 2^-24 of the product.  Results agree with an exact
+ * evaluation within 1e-5 absolute for N(0,1) inputs; the append is a bit-exact
+ * copy.
  */
 #ifndef DECODE_ATTN_H
 #define DECODE_ATTN_H

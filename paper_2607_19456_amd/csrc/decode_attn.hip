@@ -21,7 +21,7 @@
 //                          and resets the scheduling state.
 //   chunk_partial_kernel   the same pair for steps of more than 32 query rows
 //   chunk_merge_kernel     per KV head (prompt chunks), on 16-bit matrix
-//                          products of two-term sums.
+//                          products of three-term sums.
 //
 // Work decomposition of decode_partial_kernel
 //   A resident grid of 256-thread workgroups (4 waves) shares the slabs' rows:
@@ -1671,41 +1671,49 @@ __global__ __launch_bounds__(kThreads) void decode_merge_kernel(
 // Above 32 query rows per KV head the decode is bound by the matrix cores,
 // and fp32 products run there at 1/16 of the 16-bit rate.  So a workgroup
 // takes a tile of QT = 32 * NW query rows of one KV head, stages 32 keys at a
-// time in LDS -- each fp32 value as the sum of two fp16 values -- and forms
-// every product from three 16-bit ones:
-//   x = s (h + l),  h = fp16(x / s),  l = fp16(x / s - h)
-//   x y = s_x s_y (h_x h_y + h_x l_y + l_x h_y),  sums in fp32.
-// Rounding to nearest leaves |x / s - h - l| <= 2^-24 |x / s| (half an fp32
-// ulp), and the term left out is below 2^-24 |x y|; sums have 24 roundings
-// per score where the fp32 instruction's have 64, and every 32 keys' share of
-// the output is summed apart before it is added.  Against 64 bits (relative
-// 2-norm, N(0, 1) inputs): 3.4e-7 where the fp32 products had 6.2e-7 (512
-// rows x 4 heads per KV head behind 1000-7600 keys, d = 128), 1.9e-7 / 2.1e-7
-// (1500 rows of an empty cache, d = 64), 4.9e-7 / 8.4e-7 (64 rows behind
-// 60000 keys).  The scales s are powers of two that put the operands into
-// fp16's range whatever their magnitude: one per query row (largest element in
-// [2^14, 2^15)), one per visit each for K and V, raised when a tile outgrows
-// it (its first tile's largest element in [2^11, 2^12)), and 2^7 for the
-// weights, which are at most 2^8 of their reference.  Elements far below
-// their scale's largest keep an absolute error of 2^-36 of it or less.  What
-// this cannot hold -- infinities and NaN, and staged parts of a tile (64
-// lanes' share) that are not zero but below 2^-13 of the visit's scale --
-// shows at a visit's end (a non-finite sum, or a flag set while staging), and
-// the visit is then formed again in plain fp32.
+// time in LDS -- each fp32 value as the sum of three bf16 values -- and forms
+// every product from six 16-bit ones:
+//   x = h + m + l,  h = bf16(x), m = bf16(x - h), l = bf16(x - h - m)
+//   x y = h_x h_y + h_x m_y + m_x h_y + m_x m_y + h_x l_y + l_x h_y,
+// summed in fp32.  Three times 8 bits hold an fp32 significand, so the split
+// is exact (|m| <= 2^-8 |x|, |l| <= 2^-17 |x|); what is left out, m_x l_y +
+// l_x m_y + l_x l_y, is at most 2^-24 |x y| (and a small part of that on
+// average), the rounding of one fp32 operation.  bf16 has fp32's exponents, so
+// this holds for every element by itself, whatever stands beside it in its
+// row, column or tile: two-term fp16 sums, which need only three products,
+// lost what was small against their common scale.
 //
-// Matrix-bound: 2 sequences x 32/8 heads x 512 rows behind 1000-7600 keys, d =
-// 128 (86 GFLOP; 105 us at the 16-bit rate with three products for one): 296
-// us, with the fp32 products in groups of 32 rows 940 us.  Prompt of 1500
-// rows x 16 heads, d = 64: 64 us from 237.  Of a tile's 6000 cycles per SIMD
-// (two waves) 3072 are matrix work; the rest is the waves' softmax and staging
-// where it finds no partner.  Few rows gain too (8 sequences x 64/8 heads x 8
-// rows behind 2000-8000 keys 119 -> 93 us; 5 rows behind 20000-32000 293 ->
-// 222), since a tile is read and staged once for all of a KV head's rows; a
-// single row per head (T = 1) with more than 32 heads per KV head does not (8
-// x 64/1 heads behind 9000-16000 keys: 54 us with two groups of 32, 69 here)
-// and keeps the groups of 32.
+// The limits are those of the exponents:
+// - Terms below 2^-126 may be lost.  A score is off by no more than 2^-126
+//   times the other operand, far below 2^-24 as long as that is below 2^59.
+//   A weight times a value has no such yardstick, so weights (at least 2^-126
+//   where not 0) are staged times 2^24 and values times 2^30: both then keep
+//   all of their bits.
+// - Operands of 2^59 and above (infinities and NaN among them) could make
+//   sums of products overflow that do not in fp32, or 0 * inf where the split
+//   has a 0.  Staging notes tiles that hold one (K and V apart), and for these
+//   the scores or the weighted sums are formed in plain fp32 instead; so are
+//   all scores of a wave with such a query row.  Everything else runs as
+//   always, however large its spread.
 //
-// Matrix layouts (v_mfma_f32_32x32x16_f16; lane = 0..63, i = lane % 32,
+// Against 64 bits (relative 2-norm, N(0, 1) inputs): 2.7e-7 where the fp32
+// products have 6.3e-7 (512 rows x 4 heads per KV head behind 1000-7600 keys,
+// d = 128), 1.4e-7 / 2.1e-7 (1500 rows of an empty cache, d = 64).  A score's
+// leading products are summed apart from the small ones, and every 32 keys'
+// share of the output apart before it is added.
+//
+// Bound by the matrix cores and what of the waves' other work finds no partner
+// there: 2 sequences x 32/8 heads x 512 rows behind 1000-7600 keys, d = 128 (86
+// GFLOP; 210 us at the 16-bit rate with six products for one): 452 us, with
+// fp32 products in groups of 32 rows 942, with two-term fp16 sums 307.  The
+// matrix cores are busy 55 % of the time, the vector units 29 %; without
+// loads and staging it takes 430 us, and neither reading operands further
+// ahead, wave priorities, nor more loads in flight change it by more than 3 %.
+// Prompt of 1500 rows x 16 heads, d = 64: 64 us from 237.  A key of NaN adds 4
+// % to the first (its tile is formed apart); values of 2^59 and
+// above throughout make it 2.5 ms.
+//
+// Matrix layouts (v_mfma_f32_32x32x16_bf16; lane = 0..63, i = lane % 32,
 // h = lane / 32): A holds row i, B column i, both k = 8h..8h+7; D holds
 // column i, rows 8(r/4) + 4h + r%4 in component r = 0..15.  Scores are
 // S[key][query] = K Q^T, so a lane's 16 scores belong to one query, and they
@@ -1714,32 +1722,34 @@ __global__ __launch_bounds__(kThreads) void decode_merge_kernel(
 // j >= 4): V is staged transposed in that key order.
 // ---------------------------------------------------------------------------
 typedef float f2 __attribute__((ext_vector_type(2)));
-typedef _Float16 h2 __attribute__((ext_vector_type(2)));
-typedef _Float16 h8 __attribute__((ext_vector_type(8)));
+typedef __bf16 b2 __attribute__((ext_vector_type(2)));
+typedef __bf16 b8 __attribute__((ext_vector_type(8)));
 typedef float f16v __attribute__((ext_vector_type(16)));
 
 constexpr int kChunkKeys = 32;          // keys per staged tile
 constexpr int kChunkMinRows = 33;       // query rows per KV head from which the chunk kernels run
-// Keys per scheduling unit of a query tile: a visit costs about 15 us beside
-// its tiles, finer units even out more (1500 rows of an empty cache, 16 heads,
-// d = 64: 65.8 us at 32, 64.3 at 64, 66.9 at 128, 73.5 at 256; 300 rows, 32/8
-// heads, d = 128: 45.6, 33.8, 35.8, 43.2).
+// Keys per scheduling unit of a query tile: finer units even out more (8
+// sequences x 8/1 heads x 5 rows behind 4000-8000 keys, d = 128: 47 us at 64,
+// 51 at 128; chunks of 512 rows level).
 constexpr int kChunkUnit = 64;
-constexpr float kChunkLift = 128.f;     // weights are staged times this
+constexpr float kSplitMax = 0x1p59f;    // operands from here on are formed in plain fp32
+constexpr float kWeightLift = 0x1p24f;  // staged weights and values are that much larger
+constexpr float kValueLift = 0x1p30f;
 
-// Eight fp32 values times a power of two as the fp16 sum h + l.  (Packed
-// conversions: the mixed-precision multiply-adds that would do it in fewer
-// instructions take 10 cycles each here, these 4.)
-__device__ __forceinline__ void split8(const float (&x)[8], float s, h8& hi, h8& lo) {
+// Eight fp32 values as the bf16 sums h + m + l.
+__device__ __forceinline__ void split8(const float (&x)[8], b8& hi, b8& mi, b8& lo) {
 #pragma clang fp contract(off)
 #pragma unroll
   for (int e = 0; e < 8; e += 2) {
-    const f2 v = f2{x[e], x[e + 1]} * s;
-    const h2 h = __builtin_convertvector(v, h2);
-    f2 r = v - __builtin_convertvector(h, f2);
-    const h2 l = __builtin_convertvector(r, h2);
+    const f2 v = f2{x[e], x[e + 1]};
+    const b2 h = __builtin_convertvector(v, b2);
+    const f2 r = v - __builtin_convertvector(h, f2);
+    const b2 m = __builtin_convertvector(r, b2);
+    const b2 l = __builtin_convertvector(r - __builtin_convertvector(m, f2), b2);
     hi[e] = h[0];
     hi[e + 1] = h[1];
+    mi[e] = m[0];
+    mi[e + 1] = m[1];
     lo[e] = l[0];
     lo[e + 1] = l[1];
   }
@@ -1755,24 +1765,15 @@ __device__ __forceinline__ float max_abs8(const float (&x)[8]) {
   return max2(max2(m, fabsf(x[5])), max2(fabsf(x[6]), fabsf(x[7])));
 }
 
-// Exponent field of |x|, kept where the scales below are normal numbers.
-__device__ __forceinline__ int exponent_of(float x) {
-  const int e = (int)((__float_as_uint(x) >> 23) & 255u);
-  return e < 32 ? 32 : (e > 254 ? 254 : e);
-}
-// 2^(p - (e - 127)): takes a value with exponent field e to [2^p, 2^(p+1)).
-__device__ __forceinline__ float scale_to(int e, int p) {
-  return __uint_as_float((unsigned)(254 + p - e) << 23);
-}
-// Its inverse.
-__device__ __forceinline__ float scale_from(int e, int p) {
-  return __uint_as_float((unsigned)(e - p) << 23);
-}
-
 template <int CTRL>
 __device__ __forceinline__ float dpp_max(float x) {
   return max2(x, __uint_as_float(__builtin_amdgcn_update_dpp(
                      0, (int)__float_as_uint(x), CTRL, 0xf, 0xf, true)));
+}
+__device__ __forceinline__ float max_over_halves(float x) {
+  const unsigned u = __float_as_uint(x);
+  const auto a = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+  return max2(__uint_as_float(a[0]), __uint_as_float(a[1]));
 }
 __device__ __forceinline__ float max_over_wave(float x) {
   x = dpp_max<0xB1>(x);                                 // quad: lane ^ 1
@@ -1781,15 +1782,7 @@ __device__ __forceinline__ float max_over_wave(float x) {
   x = dpp_max<0x140>(x);                                // mirrored in 16
   const unsigned u = __float_as_uint(x);
   const auto a = __builtin_amdgcn_permlane16_swap(u, u, false, false);
-  x = max2(__uint_as_float(a[0]), __uint_as_float(a[1]));
-  const unsigned v = __float_as_uint(x);
-  const auto b = __builtin_amdgcn_permlane32_swap(v, v, false, false);
-  return max2(__uint_as_float(b[0]), __uint_as_float(b[1]));
-}
-__device__ __forceinline__ float max_over_halves(float x) {
-  const unsigned u = __float_as_uint(x);
-  const auto a = __builtin_amdgcn_permlane32_swap(u, u, false, false);
-  return max2(__uint_as_float(a[0]), __uint_as_float(a[1]));
+  return max_over_halves(max2(__uint_as_float(a[0]), __uint_as_float(a[1])));
 }
 // A value that all lanes hold, as a scalar (what follows from it stays on the
 // scalar unit and branches on it are not per lane).
@@ -1847,15 +1840,33 @@ void chunk_partial_kernel(const ChunkArgs a) {
   constexpr int KC = DK / 8;                            // 8-float pieces of a K row
   constexpr int KU = kChunkKeys * KC;                   // staging units of K: (key, piece)
   constexpr int VU = DV * 4;                            // of V: (dim, 8 keys)
-  constexpr int UN = KU + VU;
-  constexpr int UPT = (UN + NT - 1) / NT;
+  constexpr int KPT = (KU + NT - 1) / NT;               // units per thread
+  constexpr int VPT = (VU + NT - 1) / NT;
   constexpr int kKPiece = 16 * (kChunkKeys + 1);        // bytes between K pieces
   constexpr int kKPlane = KC * kKPiece;
   constexpr int kVPlane = 64 * DV;
-  __shared__ __align__(16) char sh_k[2][2 * kKPlane];
-  __shared__ __align__(16) char sh_v[2][2 * kVPlane];
-  __shared__ __align__(8) int sh_need[2][2];            // largest exponent of K, V staged
-  __shared__ int sh_bad;
+  // Two tiles, the next one staged while the waves work on this one, or one
+  // where two do not fit (d_k = d_v = 256).
+  constexpr int NB = 6 * (kKPlane + kVPlane) <= (160 << 10) - 64 ? 2 : 1;
+  __shared__ __align__(16) char sh_k[NB][3 * kKPlane];
+  __shared__ __align__(16) char sh_v[NB][3 * kVPlane];
+  // Where the registers of two waves per SIMD don't hold all of q, the last
+  // QL steps' low terms are kept here (spilled, their reload waits for the
+  // tile loads under way as well: chunks of 512 rows 575 us, 530 with 6 steps
+  // here).
+  constexpr int QL = DK == 128 && DV == 128 ? 7 : 0;
+  constexpr int QR = DK / 16 - QL;
+  __shared__ b8 sh_q[QL > 0 ? QL : 1][NT];
+  // Tiles with an operand of kSplitMax or above: the last of the even and of
+  // the odd ones staged (its first key; a tile's is written while the one
+  // before it is worked on), and the first and last of the visit.
+  __shared__ int sh_big[2], sh_big_lo, sh_big_hi;
+
+  // Loads of a tile are under way for a whole tile's time (kEarly), or, where
+  // registers are short, for the products between K's and V's staging (chunks
+  // of 512 rows, d = 128: 500 us and 514; 256 rows behind 20000-29000 keys, d =
+  // 256: 1448 us and 1387).
+  constexpr bool kEarly = DK + DV <= 256;
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -1931,7 +1942,7 @@ void chunk_partial_kernel(const ChunkArgs a) {
     const int64_t ue = std::min<int64_t>(u_hi, P + nt);
     const int j = static_slot(P, u, U, G, (int)blockIdx.x);
     const int nv = static_visits(P, nt, U, G);
-    const int32_t len_b = a.len[b];
+    const int32_t len_b = uniform(a.len[b]);
     const int n = decode_rows(len_b, a.n_max, app, a.T);
     const int last_row = n - 1;
     const int key0 = uniform((int)(u - P) * a.unit);
@@ -1944,6 +1955,11 @@ void chunk_partial_kernel(const ChunkArgs a) {
     const float* Vs = a.V + slab * a.n_max * DV;
     const float* Kn = app ? a.k_new + slab * a.T * DK : nullptr;
     const float* Vn = app ? a.v_new + slab * a.T * DV : nullptr;
+    // Row r of the grown cache: appended rows come from k_new / v_new.
+    auto row_at = [&](int r, const float* base, const float* nbase, int D) {
+      return (unsigned)(r - new_lo) < (unsigned)new_cnt ? nbase + (int64_t)(r - new_lo) * D
+                                                        : base + (int64_t)r * D;
+    };
 
     // This lane's query row (column i of its wave's block).
     const int x = qt * QT + 32 * wave + i;
@@ -1956,7 +1972,7 @@ void chunk_partial_kernel(const ChunkArgs a) {
     }
     // Last key any / every row of the wave sees.
     int lim_max = (int)max_over_wave((float)lim);
-    int lim_min = -(int)max_over_wave(valid ? -(float)lim : -2147483648.f);
+    int lim_min = -(int)max_over_wave(valid ? -(float)lim : -2147483520.f);
     if (a.n_max > (1 << 24)) {                          // not exact as floats
       lim_max = key1;
       lim_min = -1;
@@ -1964,123 +1980,118 @@ void chunk_partial_kernel(const ChunkArgs a) {
     lim_max = uniform(lim_max);
     lim_min = uniform(lim_min);
 
-    // ---- tile loads: staging unit (tid + y*NT) of the tile at key kt.  A
-    // wave's 64 units are rows uw/KC.. of K (uw its first unit), or 64 dims of
-    // one 8-key group of V.
-    float raw[UPT][8];
-    const int lkey = lane / KC, lc = lane % KC;
-    // (Settled at compile time where K's and V's units fill whole rounds.)
-    auto unit_k = [&](int y) {
-      if constexpr (KU % NT == 0) return y < KU / NT;
-      else return y * NT + wave * 64 < KU;
+    // ---- tile loads: a wave's 64 staging units are 64 consecutive pieces of
+    // K, or 64 dims of one 8-key group of V (keys 16(kg/2) + 4(kg%2) + 0..3
+    // and those + 8).  Where K takes fewer than all waves, V starts behind it.
+    const int vwave = (wave + NW - (KU / 64) % NW) % NW;
+    float rk[KPT][8], rv[VPT][8];
+    auto whole = [&](int kt) {
+      return kt + kChunkKeys <= new_lo ||
+             (kt >= new_lo && kt + kChunkKeys <= new_lo + new_cnt);
     };
-    auto unit_v = [&](int y) {
-      if constexpr (KU % NT == 0 && UN % NT == 0) return y >= KU / NT;
-      else return !unit_k(y) && y * NT + wave * 64 < UN;
+    auto load_k = [&](int kt) {
+      const bool w = whole(kt);
+      const float* base = kt < new_lo ? Ks + (int64_t)kt * DK : Kn + (int64_t)(kt - new_lo) * DK;
+#pragma unroll
+      for (int y = 0; y < KPT; ++y) {
+        const int uw = y * NT + wave * 64;
+        if (KU % NT != 0 && uw >= KU) continue;
+        const float* p = base + 8 * uw + 8 * lane;
+        if (!w) {
+          // Rows past the end clamp to the last row.  (The lane is made opaque
+          // so that these addresses are formed here.)
+          int ln = lane;
+          asm volatile("" : "+v"(ln));
+          p = row_at(min(kt + uw / KC + ln / KC, last_row), Ks, Kn, DK) + 8 * (ln % KC);
+        }
+        const f4 v0 = load4(p), v1 = load4(p + 4);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          rk[y][e] = v0[e];
+          rk[y][4 + e] = v1[e];
+        }
+      }
     };
-    // Where this lane's units start, from the tile's first row of K or V.
-    unsigned roff[UPT];
+    auto load_v = [&](int kt) {
+      if (whole(kt)) {
+        const float* base = kt < new_lo ? Vs + (int64_t)kt * DV : Vn + (int64_t)(kt - new_lo) * DV;
 #pragma unroll
-    for (int y = 0; y < UPT; ++y) {
-      const int uw = y * NT + wave * 64;
-      const int kg = (uw - KU) / DV;
-      roff[y] = unit_k(y) ? (uw / KC + lkey) * DK + 8 * lc
-                          : (16 * (kg >> 1) + 4 * (kg & 1)) * DV + (uw - KU) % DV + lane;
-    }
-    auto load_tile_raw = [&](int kt) {
-      const bool plain = kt + kChunkKeys <= new_lo;
-      if (plain || (kt >= new_lo && kt + kChunkKeys <= new_lo + new_cnt)) {
-        const int64_t r0 = plain ? kt : kt - new_lo;
-        const float* Kb = (plain ? Ks : Kn) + r0 * DK;
-        const float* Vb = (plain ? Vs : Vn) + r0 * DV;
+        for (int y = 0; y < VPT; ++y) {
+          const int uw = y * NT + vwave * 64;
+          if (VU % NT != 0 && uw >= VU) continue;
+          const int kg = uw / DV;
+          const float* p = base + (16 * (kg >> 1) + 4 * (kg & 1)) * DV + uw % DV;
 #pragma unroll
-        for (int y = 0; y < UPT; ++y) {
-          if (unit_k(y)) {
-            const f4 v0 = load4(Kb + roff[y]), v1 = load4(Kb + roff[y] + 4);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-              raw[y][e] = v0[e];
-              raw[y][4 + e] = v1[e];
-            }
-          } else if (unit_v(y)) {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-              raw[y][e] = (Vb + e * DV)[roff[y]];
-              raw[y][4 + e] = (Vb + (8 + e) * DV)[roff[y]];
-            }
-          }
+          for (int e = 0; e < 8; ++e) rv[y][e] = (p + ((e & 3) + 8 * (e >> 2)) * DV)[lane];
         }
         return;
       }
-      // Rows past the end clamp to the last row, appended rows come from
-      // k_new / v_new.  (The lane's indices are made opaque so that this path's
-      // addresses are formed inside it.)
-      int ln = lane;
-      asm volatile("" : "+v"(ln));
-      auto at = [&](int key, const float* base, const float* nbase, int D) {
-        const int r = min(kt + key, last_row);
-        return (unsigned)(r - new_lo) < (unsigned)new_cnt ? nbase + (int64_t)(r - new_lo) * D
-                                                          : base + (int64_t)r * D;
-      };
 #pragma unroll
-      for (int y = 0; y < UPT; ++y) {
-        const int uw = y * NT + wave * 64;
-        if (unit_k(y)) {
-          const float* p = at(uw / KC + ln / KC, Ks, Kn, DK) + 8 * (ln % KC);
-          const f4 v0 = load4(p), v1 = load4(p + 4);
+      for (int y = 0; y < VPT; ++y) {
+        const int uw = y * NT + vwave * 64;
+        if (VU % NT != 0 && uw >= VU) continue;
+        const int kg = uw / DV;
 #pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            raw[y][e] = v0[e];
-            raw[y][4 + e] = v1[e];
-          }
-        } else if (unit_v(y)) {
-          const int kg = (uw - KU) / DV;
-#pragma unroll
-          for (int e = 0; e < 8; ++e)
-            raw[y][e] = at(16 * (kg >> 1) + 4 * (kg & 1) + (e & 3) + 8 * (e >> 2), Vs, Vn,
-                           DV)[(uw - KU) % DV + ln];
+        for (int e = 0; e < 8; ++e) {
+          const int key = kt + 16 * (kg >> 1) + 4 * (kg & 1) + (e & 3) + 8 * (e >> 2);
+          rv[y][e] = row_at(min(key, last_row), Vs, Vn, DV)[uw % DV + lane];
         }
       }
     };
-    // ---- raw -> LDS with the visit's exponents xe (K, V).  Notes parts that
-    // outgrow them (for the next tile: see the loop) or fall far below.
-    int xe[2] = {32, 32};
-    auto stage = [&](int buf) {
+    // ---- into LDS as three planes (hi, mid, lo).
+    auto note = [&](const float (&x)[8], int kt) {
+      if (!__any(!(max_abs8(x) < kSplitMax))) return;
+      sh_big[(kt / kChunkKeys) & 1] = kt;
+      if (lane == 0) {
+        atomicMin(&sh_big_lo, kt);
+        atomicMax(&sh_big_hi, kt);
+      }
+    };
+    auto stage_k = [&](int buf, int kt) {
 #pragma unroll
-      for (int y = 0; y < UPT; ++y) {
+      for (int y = 0; y < KPT; ++y) {
         const int uw = y * NT + wave * 64;
-        if (!unit_k(y) && !unit_v(y)) continue;
-        const int v = unit_k(y) ? 0 : 1;
-        const float m = max_abs8(raw[y]);
-        if (__any(!(m < scale_from(min(xe[v] + 4, 255), 0))))
-          atomicMax(&sh_need[buf][v], exponent_of(m));
-        if (!__any(!(m < scale_from(xe[v] - 13, 0))) && __any(m > 0.f)) sh_bad = 1;
-        h8 hi, lo;
-        split8(raw[y], scale_to(xe[v], 11), hi, lo);
-        if (!v) {
-          char* base = sh_k[buf] + 16 * (uw / KC) + (lc * kKPiece + 16 * lkey);
-          *reinterpret_cast<h8*>(base) = hi;
-          *reinterpret_cast<h8*>(base + kKPlane) = lo;
-        } else {
-          char* base = sh_v[buf] + 16 * (uw - KU) + 16 * lane;
-          *reinterpret_cast<h8*>(base) = hi;
-          *reinterpret_cast<h8*>(base + kVPlane) = lo;
-        }
+        if (KU % NT != 0 && uw >= KU) continue;
+        note(rk[y], kt);
+        b8 hi, mi, lo;
+        split8(rk[y], hi, mi, lo);
+        char* p = sh_k[buf] + 16 * (uw / KC) + ((lane % KC) * kKPiece + 16 * (lane / KC));
+        *reinterpret_cast<b8*>(p) = hi;
+        *reinterpret_cast<b8*>(p + kKPlane) = mi;
+        *reinterpret_cast<b8*>(p + 2 * kKPlane) = lo;
+      }
+    };
+    auto stage_v = [&](int buf, int kt) {
+#pragma unroll
+      for (int y = 0; y < VPT; ++y) {
+        const int uw = y * NT + vwave * 64;
+        if (VU % NT != 0 && uw >= VU) continue;
+        note(rv[y], kt);
+        float v[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] = rv[y][e] * kValueLift;
+        b8 hi, mi, lo;
+        split8(v, hi, mi, lo);
+        char* p = sh_v[buf] + 16 * (uw + lane);
+        *reinterpret_cast<b8*>(p) = hi;
+        *reinterpret_cast<b8*>(p + kVPlane) = mi;
+        *reinterpret_cast<b8*>(p + 2 * kVPlane) = lo;
       }
     };
 
-    if (tid < 4) sh_need[tid >> 1][tid & 1] = 0;
-    if (tid == 4) sh_bad = 0;
-    load_tile_raw(key0);
+    if (tid < 2) sh_big[tid] = -1;
+    if (tid == 2) sh_big_lo = 2147483647;
+    if (tid == 3) sh_big_hi = -1;
+    load_k(key0);
+    load_v(key0);
 
-    // ---- q of the wave's rows, scaled into base-2 units and to its row's
-    // power of two, as fp16 sums: the B operand of the scores.
-    h8 qh[DK / 16], ql[DK / 16];
-    float fq;
+    // ---- q of the wave's rows, scaled into base-2 units, as bf16 sums: the B
+    // operand of the scores.
+    b8 qh[DK / 16], qm[DK / 16], ql[QR];
+    bool q_big;
     {
       const float* qr = a.q + row * DK + 8 * h;
-      float qv[DK / 16][8];
-      float m = 0.f;
+      float mx = 0.f;
 #pragma unroll
       for (int t = 0; t < DK / 16; ++t) {
         f4 v0 = f4{0.f, 0.f, 0.f, 0.f}, v1 = v0;
@@ -2088,32 +2099,28 @@ void chunk_partial_kernel(const ChunkArgs a) {
           v0 = load4(qr + 16 * t);
           v1 = load4(qr + 16 * t + 4);
         }
+        float qv[8];
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-          qv[t][e] = v0[e] * a.qscale;
-          qv[t][4 + e] = v1[e] * a.qscale;
+          qv[e] = v0[e] * a.qscale;
+          qv[4 + e] = v1[e] * a.qscale;
         }
-        m = fmaxf(m, max_abs8(qv[t]));
+        mx = max2(mx, max_abs8(qv));
+        b8 lo;
+        split8(qv, qh[t], qm[t], lo);
+        if (t < QR) ql[t] = lo;
+        else sh_q[t - QR][tid] = lo;
       }
-      const int ex = exponent_of(max_over_halves(m));
-      const float s = scale_to(ex, 14);
-      fq = scale_from(ex, 14);
-#pragma unroll
-      for (int t = 0; t < DK / 16; ++t) split8(qv[t], s, qh[t], ql[t]);
+      // (A row with a NaN comes out as NaN either way.)
+      q_big = __any(max_over_halves(mx) >= kSplitMax);
     }
-    // The first tile sets the exponents.
-    __syncthreads();                                    // sh_need, sh_bad cleared
-#pragma unroll
-    for (int y = 0; y < UPT; ++y) {
-      if (!unit_k(y) && !unit_v(y)) continue;
-      const int ex = exponent_of(max_over_wave(max_abs8(raw[y])));
-      if (lane == 0) atomicMax(&sh_need[0][unit_k(y) ? 0 : 1], ex);
+    __syncthreads();                                    // sh_big cleared
+    stage_k(0, key0);
+    stage_v(0, key0);
+    if (key0 + kChunkKeys < key1) {
+      load_k(key0 + kChunkKeys);
+      if constexpr (kEarly) load_v(key0 + kChunkKeys);
     }
-    __syncthreads();
-    xe[0] = __builtin_amdgcn_readfirstlane(sh_need[0][0]);
-    xe[1] = __builtin_amdgcn_readfirstlane(sh_need[0][1]);
-    stage(0);
-    if (key0 + kChunkKeys < key1) load_tile_raw(key0 + kChunkKeys);
     __syncthreads();
 
     float m_run = -INFINITY, l_run = 0.f;
@@ -2123,185 +2130,209 @@ void chunk_partial_kernel(const ChunkArgs a) {
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[c][r] = 0.f;
 
-    bool odd = false;
-    // O^T += V^T P for the tile in buffer vbuf; a 32-dim block's share is
-    // added while the next block's products run.
-    h8 ph[2], pl[2];
-    auto update = [&](int vbuf) {
-      const char* vb = sh_v[vbuf] + 16 * (h * DV + i);
-      h8 vh[2], vl[2];
-      auto read_v = [&](int x) {                        // step x % 2 of dims 32 (x / 2)..
-        const char* p = vb + 16 * (2 * (x & 1) * DV + 32 * (x >> 1));
-        vh[x & 1] = *reinterpret_cast<const h8*>(p);
-        vl[x & 1] = *reinterpret_cast<const h8*>(p + kVPlane);
-      };
-      read_v(0);
-      f16v o[2];
+    // ---- weights of a tile's scores (in place) against the row's reference.
+    auto weigh = [&](f16v& s, int kt) {
+      if (kt + kChunkKeys - 1 > lim_min) {
+        const int last = lim - kt - 4 * h;
 #pragma unroll
-      for (int x = 0; x < DV / 16; ++x) {
-        const int t = x & 1, c = x >> 1;
-        if (x + 1 < DV / 16) read_v(x + 1);
-        if (t == 0)
-#pragma unroll
-          for (int r = 0; r < 16; ++r) o[c & 1][r] = 0.f;
-        __builtin_amdgcn_sched_barrier(0);
-        o[c & 1] = __builtin_amdgcn_mfma_f32_32x32x16_f16(vl[t], ph[t], o[c & 1], 0, 0, 0);
-        o[c & 1] = __builtin_amdgcn_mfma_f32_32x32x16_f16(vh[t], pl[t], o[c & 1], 0, 0, 0);
-        o[c & 1] = __builtin_amdgcn_mfma_f32_32x32x16_f16(vh[t], ph[t], o[c & 1], 0, 0, 0);
-        __builtin_amdgcn_sched_barrier(0);
-        if (t == 0 && c > 0) acc[c - 1] += o[(c - 1) & 1];
+        for (int r = 0; r < 16; ++r)
+          if (8 * (r / 4) + (r & 3) > last) s[r] = -INFINITY;
       }
-      acc[DV / 32 - 1] += o[(DV / 32 - 1) & 1];
+      float tm = max2(max2(s[0], s[1]), s[2]);
+#pragma unroll
+      for (int r = 3; r < 15; r += 2) tm = max2(max2(tm, s[r]), s[r + 1]);
+      tm = max_over_halves(max2(tm, s[15]));
+      const bool bump = tm > m_run + kLazyMax;
+      if (__any(bump)) {
+        const float m_new = bump ? tm : m_run;
+        const float alpha = bump ? fast_exp2(m_run - m_new) : 1.f;
+        l_run *= alpha;
+#pragma unroll
+        for (int c = 0; c < DV / 32; ++c)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) acc[c][r] *= alpha;
+        m_run = m_new;
+      }
+      // A row that has seen no key yet exponentiates against 0.
+      const float m_ref = m_run == -INFINITY ? 0.f : m_run;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) s[r] = fast_exp2(s[r] - m_ref);
+      l_run += (((s[0] + s[1]) + (s[2] + s[3])) + ((s[4] + s[5]) + (s[6] + s[7]))) +
+               (((s[8] + s[9]) + (s[10] + s[11])) + ((s[12] + s[13]) + (s[14] + s[15])));
     };
-    // (Sending a SIMD's two waves through a tile half a turn apart -- one
-    // updating the tile before while the other forms scores -- took 3-5 %
-    // longer: the matrix unit's order of the waves does that by itself.)
+
     int buf = 0;
-    for (int kt = key0; kt < key1; kt += kChunkKeys, buf ^= 1) {
-      const int2 need = *reinterpret_cast<const int2*>(sh_need[buf]);
-      // A tile of larger values than its exponent holds: raise that, rescale
-      // the sums (V), load and stage the tile again.  (Every wave reads the
-      // same numbers: their writers passed the last barrier, the next ones of
-      // this parity wait for the next.)
-      const int nk = uniform(need.x), nvx = uniform(need.y);
-      if (nk > xe[0] + 3 || nvx > xe[1] + 3) {
-        if (nvx > xe[1] + 3) {
-          const int d = nvx - xe[1];
-          const float f = d > 100 ? 0.f : scale_to(127 + d, 0);
-          odd = odd || d > 100;
-#pragma unroll
-          for (int c = 0; c < DV / 32; ++c)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[c][r] *= f;
-          xe[1] = nvx;
-        }
-        xe[0] = max(xe[0], nk);
-        __syncthreads();                                // both read by every wave
-        load_tile_raw(kt);
-        stage(buf);
-        if (kt + kChunkKeys < key1) load_tile_raw(kt + kChunkKeys);
-        __syncthreads();
-      }
-      const float fs = fq * scale_from(xe[0], 11);
+    for (int kt = key0; kt < key1; kt += kChunkKeys, buf ^= NB - 1) {
       const bool more = kt + kChunkKeys < key1;
-      auto stage_next = [&] {
-        stage(buf ^ 1);
-        if (kt + 2 * kChunkKeys < key1) load_tile_raw(kt + 2 * kChunkKeys);
-      };
-      if (kt <= lim_max) {
+      const bool seen = kt <= lim_max && !q_big && uniform(sh_big[(kt / kChunkKeys) & 1]) != kt;
+      f16v s;
+      if (seen) {
         const char* kb = sh_k[buf] + h * kKPiece + 16 * i;
-        f16v s;
+        // The leading products' sum, and that of the small ones.
+        f16v sm;
 #pragma unroll
-        for (int r = 0; r < 16; ++r) s[r] = 0.f;
-        // (Each step's operands are read a step ahead of their products.)
-        h8 kh[2], kl[2];
-        auto read_k = [&](int t) {
-          kh[t & 1] = *reinterpret_cast<const h8*>(kb + 2 * t * kKPiece);
-          kl[t & 1] = *reinterpret_cast<const h8*>(kb + 2 * t * kKPiece + kKPlane);
+        for (int r = 0; r < 16; ++r) s[r] = sm[r] = 0.f;
+        // (Each plane of the next step is read as soon as this step's is used.)
+        b8 kh, km, kl;
+        auto read_k = [&](int t, int plane) {
+          return *reinterpret_cast<const b8*>(kb + 2 * t * kKPiece + plane * kKPlane);
         };
-        read_k(0);
+        kl = read_k(0, 2);
+        km = read_k(0, 1);
+        kh = read_k(0, 0);
 #pragma unroll
         for (int t = 0; t < DK / 16; ++t) {
-          if (t + 1 < DK / 16) read_k(t + 1);
+          const bool next = t + 1 < DK / 16;
+          const b8 lq = t < QR ? ql[t < QR ? t : 0] : sh_q[t < QR ? 0 : t - QR][tid];
+          sm = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kl, qh[t], sm, 0, 0, 0);
           __builtin_amdgcn_sched_barrier(0);
-          s = __builtin_amdgcn_mfma_f32_32x32x16_f16(kl[t & 1], qh[t], s, 0, 0, 0);
-          s = __builtin_amdgcn_mfma_f32_32x32x16_f16(kh[t & 1], ql[t], s, 0, 0, 0);
-          s = __builtin_amdgcn_mfma_f32_32x32x16_f16(kh[t & 1], qh[t], s, 0, 0, 0);
+          if (next) kl = read_k(t + 1, 2);
+          sm = __builtin_amdgcn_mfma_f32_32x32x16_bf16(km, qm[t], sm, 0, 0, 0);
+          sm = __builtin_amdgcn_mfma_f32_32x32x16_bf16(km, qh[t], sm, 0, 0, 0);
           __builtin_amdgcn_sched_barrier(0);
+          if (next) km = read_k(t + 1, 1);
+          sm = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kh, lq, sm, 0, 0, 0);
+          sm = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kh, qm[t], sm, 0, 0, 0);
+          s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kh, qh[t], s, 0, 0, 0);
+          __builtin_amdgcn_sched_barrier(0);
+          if (next) kh = read_k(t + 1, 0);
         }
-        if (kt + kChunkKeys - 1 > lim_min) {
-          const int seen = lim - kt - 4 * h;
-#pragma unroll
-          for (int r = 0; r < 16; ++r)
-            if (8 * (r / 4) + (r & 3) > seen) s[r] = -INFINITY;
-        }
-        float tm = max2(max2(s[0], s[1]), s[2]);
-#pragma unroll
-        for (int r = 3; r < 15; r += 2) tm = max2(max2(tm, s[r]), s[r + 1]);
-        tm = max_over_halves(max2(tm, s[15])) * fs;
-        const bool bump = tm > m_run + kLazyMax;
-        if (__any(bump)) {
-          const float m_new = bump ? tm : m_run;
-          const float alpha = bump ? fast_exp2(m_run - m_new) : 1.f;
-          l_run *= alpha;
-#pragma unroll
-          for (int c = 0; c < DV / 32; ++c)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[c][r] *= alpha;
-          m_run = m_new;
-        }
-        // A row that has seen no key yet exponentiates against 0.
-        const float m_ref = m_run == -INFINITY ? 0.f : m_run;
-        float psum = 0.f;
+        s += sm;
+      }
+      if constexpr (NB == 1) __syncthreads();           // K's buffer is free
+      if (more) {
+        stage_k(buf ^ (NB - 1), kt + kChunkKeys);
+        if constexpr (!kEarly) load_v(kt + kChunkKeys);
+        else if (kt + 2 * kChunkKeys < key1) load_k(kt + 2 * kChunkKeys);
+      }
+      if (seen) {
+        weigh(s, kt);
+        b8 ph[2], pm[2], pl[2];
 #pragma unroll
         for (int t = 0; t < 2; ++t) {
           float p[8];
 #pragma unroll
-          for (int e = 0; e < 8; ++e) p[e] = fast_exp2(__builtin_fmaf(s[8 * t + e], fs, -m_ref));
-          psum += ((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7]));
-          split8(p, kChunkLift, ph[t], pl[t]);
+          for (int e = 0; e < 8; ++e) p[e] = s[8 * t + e] * kWeightLift;
+          split8(p, ph[t], pm[t], pl[t]);
         }
-        l_run += psum;
-        update(buf);
+        // O^T += V^T P, a block of 32 dims at a time.
+        const char* vb = sh_v[buf] + 16 * (h * DV + i);
+        b8 vh, vm, vl;
+        auto read_v = [&](int x, int plane) {         // step x % 2 of dims 32 (x / 2)..
+          return *reinterpret_cast<const b8*>(vb + 16 * (2 * (x & 1) * DV + 32 * (x >> 1)) +
+                                              plane * kVPlane);
+        };
+        vl = read_v(0, 2);
+        vm = read_v(0, 1);
+        vh = read_v(0, 0);
+        f16v o;
+#pragma unroll
+        for (int x = 0; x < DV / 16; ++x) {
+          const int t = x & 1, c = x >> 1;
+          const bool next = x + 1 < DV / 16;
+          if (t == 0)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) o[r] = 0.f;
+          o = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vl, ph[t], o, 0, 0, 0);
+          __builtin_amdgcn_sched_barrier(0);
+          if (next) vl = read_v(x + 1, 2);
+          o = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vm, pm[t], o, 0, 0, 0);
+          o = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vm, ph[t], o, 0, 0, 0);
+          __builtin_amdgcn_sched_barrier(0);
+          if (next) vm = read_v(x + 1, 1);
+          o = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vh, pl[t], o, 0, 0, 0);
+          o = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vh, pm[t], o, 0, 0, 0);
+          o = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vh, ph[t], o, 0, 0, 0);
+          __builtin_amdgcn_sched_barrier(0);
+          if (next) vh = read_v(x + 1, 0);
+          if (t == 1)
+#pragma unroll
+            for (int r = 0; r < 16; ++r)
+              acc[c][r] = __builtin_fmaf(o[r], 1.f / (kWeightLift * kValueLift), acc[c][r]);
+        }
       }
-      if (more) stage_next();
+      if constexpr (NB == 1) __syncthreads();           // V's buffer is free
+      if (more) {
+        stage_v(buf ^ (NB - 1), kt + kChunkKeys);
+        if (kt + 2 * kChunkKeys < key1) {
+          if constexpr (kEarly) load_v(kt + 2 * kChunkKeys);
+          else load_k(kt + 2 * kChunkKeys);
+        }
+      }
       __syncthreads();
     }
 
-    // ---- the visit's partial.
-    float L = sum_over_halves(l_run);
-    float of = scale_from(xe[1], 11) * (1.f / kChunkLift);
-    odd = odd || sh_bad != 0;
-    {
-      // A sum that is not finite stays so under this one (x - x is 0 or NaN).
-      float z = L - L;
-#pragma unroll
-      for (int c = 0; c < DV / 32; ++c)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) z += acc[c][r] - acc[c][r];
-      odd = odd || (valid && !(z == 0.f));
+    // ---- the tiles left out above, in fp32 products from memory.
+    int kt_big = uniform(sh_big_lo), kt_end = min(uniform(sh_big_hi), lim_max);
+    if (q_big) {
+      kt_big = key0;
+      kt_end = min(key1 - 1, lim_max);
     }
-    if (__any(odd)) {
-      // In plain fp32, one key after the other: both halves of a row's lanes
-      // form half of its score, and each sums the dims it holds.
-      L = 0.f;
-      m_run = -INFINITY;
-      of = 1.f;
-#pragma unroll
-      for (int c = 0; c < DV / 32; ++c)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc[c][r] = 0.f;
-      const float* qr = a.q + (valid ? row : slab * a.R) * DK + h * (DK / 2);
-      for (int key = key0; key < key1; ++key) {
-        const bool isnew = (unsigned)(key - new_lo) < (unsigned)new_cnt;
-        const float* kr = isnew ? Kn + (int64_t)(key - new_lo) * DK : Ks + (int64_t)key * DK;
-        const float* vr = isnew ? Vn + (int64_t)(key - new_lo) * DV : Vs + (int64_t)key * DV;
-        float s = 0.f;
+    for (; kt_big <= kt_end; kt_big += kChunkKeys) {
+      const int kt = kt_big;
+      if (!q_big) {
+        float mx = 0.f;
+        auto look = [&](const float* base, const float* nbase, int D) {
 #pragma unroll 4
-        for (int d = 0; d < DK / 2; ++d)
-          s = __builtin_fmaf(qr[d] * a.qscale, kr[h * (DK / 2) + d], s);
-        s = sum_over_halves(s);
-        if (key <= lim) {
-          if (s > m_run) {
-            const float alpha = fast_exp2(m_run - s);   // 0 for the first
-            L *= alpha;
+          for (int e = 4 * lane; e < kChunkKeys * D; e += 256) {
+            const f4 v = load4(row_at(min(kt + e / D, last_row), base, nbase, D) + e % D);
+            mx = max2(max2(mx, fabsf(v[0])), max2(max2(fabsf(v[1]), fabsf(v[2])), fabsf(v[3])));
+          }
+        };
+        look(Ks, Kn, DK);
+        look(Vs, Vn, DV);
+        if (!__any(!(mx < kSplitMax))) continue;        // staged, and done
+      }
+      f16v s;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) s[r] = 0.f;
+      // (32x32x2 products: a lane's k is h; step e of a group takes dims
+      // 8 g + e and 8 g + 4 + e.)
+      const float* kr = row_at(min(kt + i, last_row), Ks, Kn, DK) + 4 * h;
+      const float* qr = a.q + (valid ? row : slab * a.R) * DK + 4 * h;
+#pragma unroll 4
+      for (int d = 0; d < DK; d += 8) {
+        const f4 kv = load4(kr + d), qv = load4(qr + d) * a.qscale;
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          s = __builtin_amdgcn_mfma_f32_32x32x2f32(kv[e], qv[e], s, 0, 0, 0);
+      }
+      weigh(s, kt);
+      if (kt + kChunkKeys - 1 <= lim_min) {
+#pragma unroll
+        for (int c = 0; c < DV / 32; ++c)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) {
+            const int key = kt + 8 * (r / 4) + 4 * h + (r & 3);
+            const float v = row_at(min(key, last_row), Vs, Vn, DV)[32 * c + i];
+            acc[c] = __builtin_amdgcn_mfma_f32_32x32x2f32(v, s[r], acc[c], 0, 0, 0);
+          }
+      } else {
+        // Some rows do not see all of it: one key after the other, so that
+        // what they do not see takes no part in them (0 * inf is NaN).
+#pragma unroll 1
+        for (int y = 0; y < kChunkKeys; ++y) {
+          float p = 0.f;
+#pragma unroll
+          for (int r = 0; r < 16; ++r)
+            if (r == 4 * (y >> 3) + (y & 3)) p = s[r];
+          const unsigned pu = __float_as_uint(p);
+          const auto both = __builtin_amdgcn_permlane32_swap(pu, pu, false, false);
+          p = __uint_as_float((y >> 2) & 1 ? both[1] : both[0]);
+          const float* vr = row_at(min(kt + y, last_row), Vs, Vn, DV) + 4 * h;
+          if (kt + y <= lim) {
 #pragma unroll
             for (int c = 0; c < DV / 32; ++c)
 #pragma unroll
-              for (int r = 0; r < 16; ++r) acc[c][r] *= alpha;
-            m_run = s;
+              for (int r = 0; r < 16; ++r)
+                acc[c][r] = __builtin_fmaf(p, vr[32 * c + 8 * (r / 4) + (r & 3)], acc[c][r]);
           }
-          // (A NaN score makes the row NaN; scores of -inf have no weight.)
-          const float p = s == -INFINITY ? 0.f : fast_exp2(s - m_run);
-          L += p;
-#pragma unroll
-          for (int c = 0; c < DV / 32; ++c)
-#pragma unroll
-            for (int r = 0; r < 16; ++r)
-              acc[c][r] = __builtin_fmaf(p, vr[32 * c + 8 * (r / 4) + 4 * h + (r & 3)], acc[c][r]);
         }
       }
     }
+
+    // ---- the visit's partial.
+    const float L = sum_over_halves(l_run);
     if (valid) {
       const int64_t slot = row * a.J + j;
       if (h == 0) {
@@ -2314,7 +2345,7 @@ void chunk_partial_kernel(const ChunkArgs a) {
 #pragma unroll
         for (int rb = 0; rb < 4; ++rb)
           *reinterpret_cast<f4*>(dst + 32 * c + 8 * rb) =
-              f4{acc[c][4 * rb], acc[c][4 * rb + 1], acc[c][4 * rb + 2], acc[c][4 * rb + 3]} * of;
+              f4{acc[c][4 * rb], acc[c][4 * rb + 1], acc[c][4 * rb + 2], acc[c][4 * rb + 3]};
     }
 
     u = ue;
@@ -2695,8 +2726,8 @@ void launch_chunk_nw(ChunkArgs a, int resident, hipStream_t s) {
   // Whole items where the slots don't allow a split.
   a.unit = a.J >= 3 ? kChunkUnit : (int)(ceil_div(a.n_max, kChunkKeys) * kChunkKeys);
   const int64_t units = (int64_t)a.B * a.nqt * a.h_kv * ceil_div(a.n_max, a.unit);
-    hipLaunchKernelGGL((chunk_partial_kernel<DK, DV, NW>), dim3((unsigned)std::min<int64_t>(units, resident)),
-                     dim3(64 * NW), 0, s, a);
+  hipLaunchKernelGGL((chunk_partial_kernel<DK, DV, NW>),
+                     dim3((unsigned)std::min<int64_t>(units, resident)), dim3(64 * NW), 0, s, a);
 }
 
 template <int DK, int DV>
