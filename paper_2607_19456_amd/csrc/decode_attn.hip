@@ -2379,16 +2379,27 @@ __global__ __launch_bounds__(kThreads) void chunk_merge_kernel(
     const float* acc = ws_acc + row * J * DV + 4 * ch;
     float m = -INFINITY, l = 0.f;
     f4 o = f4{0.f, 0.f, 0.f, 0.f};
-    for (int j = 0; j < nv; ++j) {
-      const float2 st = ml[j];
-      const f4 v = load4(acc + (int64_t)j * DV);
-      if (st.x == -INFINITY && st.y == 0.f) continue;   // a visit that saw no key
-      const float mn = fmaxf(m, st.x);
-      const float wo = mn == m ? 1.f : fast_exp2(m - mn);
-      const float wn = mn == st.x ? 1.f : fast_exp2(st.x - mn);
-      l = l * wo + st.y * wn;
-      o = o * wo + v * wn;
-      m = mn;
+    // Four at a time, so that their loads share a round trip.
+    for (int j0 = 0; j0 < nv; j0 += 4) {
+      float2 st[4];
+      f4 v[4];
+#pragma unroll
+      for (int y = 0; y < 4; ++y) {
+        const int j = min(j0 + y, nv - 1);
+        st[y] = ml[j];
+        v[y] = load4(acc + (int64_t)j * DV);
+      }
+#pragma unroll
+      for (int y = 0; y < 4; ++y) {
+        if (j0 + y >= nv) break;
+        if (st[y].x == -INFINITY && st[y].y == 0.f) continue;   // a visit that saw no key
+        const float mn = fmaxf(m, st[y].x);
+        const float wo = mn == m ? 1.f : fast_exp2(m - mn);
+        const float wn = mn == st[y].x ? 1.f : fast_exp2(st[y].x - mn);
+        l = l * wo + st[y].y * wn;
+        o = o * wo + v[y] * wn;
+        m = mn;
+      }
     }
     *reinterpret_cast<f4*>(out + row * DV + 4 * ch) =
         l == 0.f ? f4{0.f, 0.f, 0.f, 0.f} : o / l;
