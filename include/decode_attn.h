@@ -223,13 +223,15 @@ da_status da_decode_merge(float *out, int32_t *len, int B, int h_q, int h_kv,
  * with p < 0 gives 0.  T = 1 is da_decode_attn.
  *     q   float [B][h_q][T][d_k]      out float [B][h_q][T][d_v]
  * The T rows of every query head of a group are scored from the same K/V
- * reads (the kernels treat them as h_q*T query heads; from 33 of them per KV
- * head on in kernels of their own, which skip what no row of a tile sees), so
- * the workspace is
- * that of a single-row decode with h_q*T query heads:
+ * reads (the kernels treat them as h_q*T query heads; more than 32 of them per
+ * KV head, where there is enough work, go to kernels of their own, which skip
+ * what no row of a tile sees), so the workspace is that of a single-row decode
+ * with h_q*T query heads:
  * da_decode_workspace_bytes(B, h_q*T, h_kv, ...) bytes, its counter region
  * da_decode_workspace_counter_bytes(B, h_q*T, h_kv, ...).  T <= 4096.  Other
- * rules as da_decode_attn.
+ * rules as da_decode_attn.  Rows of V that a query row does not see have weight
+ * 0 in it: they must be finite, as 0 * inf is NaN (the kernels for many query
+ * rows leave them out, the others do not).
  */
 da_status da_decode_multi(const float *q, const float *K, const float *V,
                           const int32_t *len, float scale, float *out, int B,

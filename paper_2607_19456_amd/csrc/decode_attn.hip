@@ -19,9 +19,9 @@
 //                          len (the whole step in one launch).
 //   decode_merge_kernel    combines each head's partials into its output row
 //                          and resets the scheduling state.
-//   chunk_partial_kernel   the same pair for steps of more than 32 query rows
-//   chunk_merge_kernel     per KV head (prompt chunks), on 16-bit matrix
-//                          products of three-term sums.
+//   chunk_partial_kernel   the same pair for steps of many query rows per KV
+//   chunk_merge_kernel     head (prompt chunks), on 16-bit matrix products of
+//                          three-term sums.
 //
 // Work decomposition of decode_partial_kernel
 //   A resident grid of 256-thread workgroups (4 waves) shares the slabs' rows:
@@ -1727,7 +1727,6 @@ typedef __bf16 b8 __attribute__((ext_vector_type(8)));
 typedef float f16v __attribute__((ext_vector_type(16)));
 
 constexpr int kChunkKeys = 32;          // keys per staged tile
-constexpr int kChunkMinRows = 33;       // query rows per KV head from which the chunk kernels run
 // Keys per scheduling unit of a query tile: finer units even out more (8
 // sequences x 8/1 heads x 5 rows behind 4000-8000 keys, d = 128: 47 us at 64,
 // 51 at 128; chunks of 512 rows level).
@@ -2731,6 +2730,39 @@ void launch_partial_nb(const Plan& pl, const PartialArgs& a, const WsView& w, hi
 }
 
 // ---- chunk kernels (more than 32 query rows per KV head) --------------------
+// Where the chunk kernels are the faster ones, for R query rows per KV head and
+// d = d_k + d_v: a tile is read and staged once for all of a KV head's rows,
+// where the decode reads it for every group of 32, but a visit and the merge
+// cost more.  Measured over 455 shapes of 2-256 slabs (sequences x KV heads) x
+// 200-6000 rows x 40-1024 query rows per KV head (decode / chunk, us):
+// - Up to two groups read each row once or twice: the decode's, except in
+//   large batches of short caches (128 slabs x 900 rows, R = 40, d = 128 each:
+//   25 % slower than the chunk kernels; 32 slabs x 20000-29000 272 / 290; 8 x
+//   16000 55 / 65).
+// - With fewer than three slots an item is not cut, so its workgroup's time is
+//   the launch's: from more than one of the decode's groups per CU on (768 rows
+//   in d = 64 caches: 16 slabs x 700 rows 83 / 69; 600 rows, d = 128: 32 slabs x
+//   R = 200, 224 groups, 0.62 of the decode's speed, 64 x 200, 448 groups, 1.05;
+//   d = 512: 128 x 96, 384 groups, 0.94, 128 x 200, 896 groups, 1.65).
+// - Else all batches of 32 slabs and more (1.04-5 times as fast, one shape of
+//   d = 512 0.97), and smaller ones of enough work: rows x query rows, and as
+//   much more as there are fewer items, whose visits the merge has to combine
+//   one after the other (d = 256: 8 slabs x 8300 rows, R = 96: 50 / 50, R = 128:
+//   57 / 51; 2 x 6000, R = 400: 1.08, 2 x 11400, R = 192: 48 / 58; 1 x 130000, R
+//   = 96: 86 / 121, R = 256: 165 / 150; d = 128: 8 x 8300, R = 96: 33 / 38, R =
+//   256 54 / 48).
+// One query row per head (T = 1) stays with the decode.
+bool chunk_pays(int B, int h_kv, int R, int n_max, int d, int J) {
+  const int64_t slabs = (int64_t)B * h_kv;
+  const int64_t groups = ceil_div(R, kHeadsPerGroup);
+  if (groups < 2) return false;
+  if (J < 3) return slabs * groups > (d <= 256 ? 320 : 512);
+  if (groups == 2) return d <= 256 && slabs >= 128 && n_max <= kDirectMaxRows;
+  if (slabs >= 32) return true;
+  const int64_t items = slabs * ceil_div(R, d <= 256 ? 256 : 128);
+  return slabs * R * n_max * std::min<int64_t>(items, 8) >= ((int64_t)(d >= 256 ? 24 : 64) << 20);
+}
+
 template <int DK, int DV, int NW>
 void launch_chunk_nw(ChunkArgs a, int resident, hipStream_t s) {
   a.nqt = (int)ceil_div(a.R, 32 * NW);
@@ -2801,7 +2833,8 @@ da_status partial_impl(const float* q, const float* K, const float* V, const flo
                       scale * kLog2e, B, rows, h_kv, n_max, T, direct, bump};
   hipStream_t s = static_cast<hipStream_t>(stream);
   (void)hipGetLastError();
-  if (allow_direct && chunk_rows == 0 && T > 1 && rows / h_kv >= kChunkMinRows) {
+  if (allow_direct && chunk_rows == 0 && T > 1 &&
+      chunk_pays(B, h_kv, rows / h_kv, n_max, d_k + d_v, pl.J)) {
     if (out_plan) out_plan->chunked = true;
     const ChunkArgs c{q, const_cast<float*>(K), const_cast<float*>(V), k_new, v_new, len,
                       scale * kLog2e, B, h_kv, n_max, T, rows / h_kv, 0, 0, pl.J, w.nvis, w.ml,

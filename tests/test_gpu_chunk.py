@@ -1,12 +1,14 @@
-"""The chunk kernels (more than 32 query rows per KV head, T > 1) against the
-oracle: edges of the query tiles and key tiles, every pair of head sizes,
-ragged, empty and clipped lengths, items cut over many workgroups and items
-that may not be cut, and values that the 16-bit operands cannot hold as they
-are: magnitudes far from 1, growing and falling ones, infinities and NaN.
+"""Steps of more than 32 query rows per KV head (T > 1) against the oracle:
+edges of the query tiles and key tiles, every pair of head sizes, ragged,
+empty and clipped lengths, items cut over many workgroups and items that may
+not be cut, and values that need care as 16-bit operands: magnitudes far from
+1, growing and falling ones, infinities and NaN.  The small shapes stay with
+the decode kernels; the ones after them, and BASE, take the chunk kernels.
 
 Tolerance: 1e-5 of V's largest magnitude, as for the other decodes at N(0, 1)
 (values of about 4: the fp32 sums of at most a few thousand terms and the
-dropped products, 2^-24 of each term, stay below 1e-6 of it)."""
+products that are left out, at most 2^-24 of each term, stay below 1e-6 of
+it)."""
 import numpy as np
 import pytest
 import torch
@@ -99,6 +101,21 @@ SHAPES = [
     (300, 2, 2, 64, 64, 90, 40, [(7 * b) % 91 for b in range(300)]),   # items may not be cut
     (1, 4, 1, 64, 64, 40000, 10, [39985]),                # more units than slots
     (1, 2, 1, 64, 64, 3000, 2048, [952]),                 # many query tiles
+    # Enough work for the chunk kernels.
+    (32, 5, 1, 128, 128, 900, 13, [33, 0, 31, 32, 800, 887, 890, -2] * 4),   # 65 rows: the fewest
+    (32, 1, 1, 128, 128, 900, 256, [31, 0, 32, 643, 644, 700, 899, 900] * 4),    # one whole tile
+    (16, 4, 2, 128, 128, 800, 129, [32, 443] * 8),        # two rows in the second; across heads
+    (32, 2, 1, 64, 64, 1000, 100, [0, 900] * 16),
+    (32, 4, 1, 64, 128, 800, 20, [129, 77] * 16),
+    (32, 4, 1, 128, 64, 800, 20, [128, 380] * 16),
+    (16, 4, 2, 64, 256, 800, 33, [300, 799] * 8),
+    (16, 4, 2, 256, 64, 800, 33, [301, 0] * 8),
+    (16, 4, 2, 128, 256, 800, 33, [95, 97] * 8),
+    (16, 4, 2, 256, 128, 800, 33, [96, 3] * 8),
+    (16, 4, 2, 256, 256, 900, 70, [640, 1] * 8),
+    (128, 8, 1, 64, 64, 1100, 5, [(9 * b) % 1101 for b in range(128)]),  # two groups, short caches
+    (180, 2, 1, 256, 256, 90, 40, [b % 91 for b in range(180)]),  # items may not be cut
+    (1, 8, 1, 64, 64, 40000, 128, [39800]),               # more units than slots
 ]
 
 
@@ -107,7 +124,7 @@ def test_chunk_shapes(cuda_device, shape):
     run_both(*shape)
 
 
-BASE = (1, 4, 1, 128, 128, 600, 40, [500])
+BASE = (32, 4, 1, 128, 128, 800, 40, [500] * 32)
 
 
 def scaled(kf, qf, vf):
