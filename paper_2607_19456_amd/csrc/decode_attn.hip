@@ -834,10 +834,9 @@ __device__ __forceinline__ void process_tile(const Tile<DK, DV, NB>& T, int row0
 // Static part of the schedule.
 //
 // Rows are scheduled in units of Cd rows (one turn of the tile ring for all
-// four waves; in some wholly static plans one tile of each).  Every slab of sequence b holds st(b) = floor(fnum/16 * n_b /
+// four waves).  Every slab of sequence b holds st(b) = floor(fnum/16 * n_b /
 // Cd) static units at its start (ceil(n_b / Cd), all of it, for fnum = 16);
-// the rest of its rows is its dynamic part,
-// handed out one unit at a time.  The static units of all slabs, in slab
+// the rest of its rows is its dynamic part, handed out one unit at a time.  The static units of all slabs, in slab
 // order, form one space of Ru units that is cut into gridDim.x contiguous
 // ranges, [w*Ru/G, (w+1)*Ru/G) for workgroup w: the ranges are proportional
 // to the rows, so every workgroup starts with the same amount of work (to
@@ -1399,8 +1398,7 @@ __global__ __launch_bounds__(kThreads, W) void decode_partial_kernel(
           for (int p = 0; p < R; ++p) {
             const int r = row_of(t + p);
             load(ring[(p + R - 1) % R], row_of(t + p + R - 1), last_row);
-            // (Only a visit's last segment may end inside a turn.)
-            if (r <= last_row && (p == 0 || t + p < ctpw)) {
+            if (r <= last_row) {
               if constexpr (PAIRS)
                 process_tile_pairs<DK, DV, NB, CAUSAL, kPin>(ring[p], r, lim, src, lane,
                                                              sh_k[PAIRS ? wave : 0], sh_q, qr,
@@ -2558,8 +2556,7 @@ da_status plan_chunks(int B, int h_q, int h_kv, int n_max, int d_k, int d_v, int
     plan->fnum = kStaticDen;
   }
   // Scheduling units (static ranges and dynamic hand-outs) are one ring turn
-  // of the four waves when there is a static share, else whole chunks
-  // (refine_grid makes some wholly static plans' smaller).
+  // of the four waves when there is a static share, else whole chunks.
   const int ring = plan->two_waves ? 2 : ring_tiles(plan->blocks, d_k, d_v);
   plan->dyn_rows = plan->fnum > 0 ? ring * kWaves * kTileRows : chunk_rows;
   // Static slots: at most one per static unit of a slab plus one, and never
@@ -2596,29 +2593,21 @@ da_status plan_chunks(int B, int h_q, int h_kv, int n_max, int d_k, int d_v, int
 // one per CU, and kMaxSlabVisitors per slab, where the chunks ask for fewer:
 // with two per CU a batch of that size merges twice the visits of half the
 // length (8 sequences of 4222-4802 rows, 4/4 heads 34.4 us in chunks, 34.5 at
-// one per CU, 37.9 at two; 6 of 3000-6000, 16/4 heads 29.3, 28.4, 31.5).
+// one per CU, 37.9 at two; 6 of 3000-6000, 16/4 heads 29.3, 28.4, 31.5).  Where
+// the chunks occupy more than two thirds of the CUs they stay: slabs of a few
+// equal chunks each would only be cut less evenly (18 sequences of 4712 rows,
+// 32/1 heads, two rows a step, 252 chunks: 49.4 us, 55.8 in 256 ranges; 47 of
+// 1080, 8/2 heads, 188 chunks: 30.5 and 33.1; over 120-160 chunks the ranges
+// gain 8-16 %).
 constexpr int kMinRangeRows = 128;
-void refine_grid(int n_max, int d_k, int d_v, int resident, Plan* plan) {
+void refine_grid(int n_max, int resident, Plan* plan) {
+  if (3 * plan->grid > 2 * resident) return;
   const int64_t per_slab = ceil_div(n_max, kMinRangeRows);
   int64_t grid = std::min<int64_t>(resident, plan->slabs * per_slab);
   if (plan->two_waves)
     grid = std::max<int64_t>(plan->grid,
                              std::min<int64_t>(grid, plan->slabs * (int64_t)kMaxSlabVisitors));
   plan->grid = (int)std::max<int64_t>(1, grid);
-  // Its units: single tiles of the four waves (64 rows) instead of ring turns
-  // where turns are long against a workgroup's share -- the four-tile turns of
-  // two column blocks (MQA, 64 sequences of 512-8192 rows 78.0 -> 74.5 us; 2 x
-  // 600 rows 25.6 -> 21.3) and the two-wave form from two turns per workgroup
-  // on (16 ragged sequences of 200-4000 rows, 32/8 heads 50.7 -> 50.0; four
-  // rows a step, 8 sequences 42.1 -> 40.9).  A visit that ends inside a turn
-  // pays for all of it: one turn or less per workgroup (one sequence of 2900
-  // rows 17.4 and 18.1), heads of 64 (30 sequences of 3000 rows 69.6 and 70.5)
-  // and the two-tile turns of one column block at one per CU (d = 256, 4
-  // sequences 79.5 and 82.0) keep turns.
-  const bool turns_long = plan->blocks == 2 && plan->dyn_rows == 4 * kWaves * kTileRows;
-  const bool turns_many = plan->two_waves && d_k + d_v > 128 &&
-                          plan->slabs * per_slab >= 2 * (int64_t)plan->grid;
-  if (turns_long || turns_many) plan->dyn_rows = kWaves * kTileRows;
 }
 
 // The plan of a call: plan_chunks', refined where the library chooses the
@@ -2630,7 +2619,7 @@ da_status make_plan(int B, int h_q, int h_kv, int n_max, int d_k, int d_v, int c
   const da_status st = plan_chunks(B, h_q, h_kv, n_max, d_k, d_v, chunk_rows, resident, plan);
   if (st != DA_OK || chunk_rows != 0 || B > kMaxStaticSeqs) return st;
   if (!plan->single_chunk) {
-    if (plan->fnum == kStaticDen) refine_grid(n_max, d_k, d_v, resident, plan);
+    if (plan->fnum == kStaticDen) refine_grid(n_max, resident, plan);
   } else if (plan->slabs <= kSplitMaxSlabs && (int64_t)n_max * (d_k + d_v) >= kSplitMinFloats) {
     // A slot for every kMinRangeRows rows; the library's own workspace goes on
     // holding what it held.
@@ -2642,7 +2631,7 @@ da_status make_plan(int B, int h_q, int h_kv, int n_max, int d_k, int d_v, int c
         (split.two_waves ? 2 : ring_tiles(plan->blocks, d_k, d_v)) * kWaves * kTileRows;
     split.Jd = 1;
     split.J = (int)ceil_div(n_max, kMinRangeRows) + 2;
-    refine_grid(n_max, d_k, d_v, resident, &split);
+    refine_grid(n_max, resident, &split);
     size_plan(B, h_q, d_v, &split);
     if (split.bytes <= kScratchBytes) *plan = split;
   }

@@ -18,14 +18,19 @@ SHAPES = [
     (13, 10, 5, 128, 128, 513, [512] * 12 + [7]),                      # 65 slabs
     (2, 32, 1, 128, 128, 700, [699, 255]),       # two column blocks
     (2, 4, 2, 256, 256, 256, [255, 3]),
-    (1, 8, 1, 64, 64, 16384, [16383]),           # as many visitors as a slab may have
-    (1, 8, 1, 64, 64, 16513, [16512]),           # more units than that
+    (1, 8, 1, 64, 64, 32768, [32767]),           # as many visitors as a slab may have
+    # More units in the slab than it has slots: fewer workgroups take part.
+    (1, 8, 1, 64, 64, 16384, [16383]),
+    (1, 8, 1, 64, 64, 16513, [16512]),
+    (1, 4, 1, 256, 256, 16384, [16383]),
     (3, 2, 1, 64, 64, 2000, [0, 0, 1]),          # almost nothing to do
-    # Units of single tiles, more of them in one slab than it has slots: fewer
-    # workgroups take part.
+    # All rows in one sequence of many; two column blocks.
     (16, 8, 8, 64, 64, 4096, [4095] + [0] * 15),
     (8, 32, 1, 64, 64, 8192, [0] * 7 + [8190]),
-    (8, 32, 1, 64, 64, 2049, [2048, 64, 65, 63, 0, 1, 2000, 1030]),    # visits end inside turns
+    (8, 32, 1, 64, 64, 2049, [2048, 64, 65, 63, 0, 1, 2000, 1030]),
+    # Chunks on two thirds of 256 CUs, and on one more: ranges and chunks.
+    (17, 8, 2, 128, 128, 3800, [3799 - 13 * b for b in range(17)]),
+    (19, 3, 3, 64, 64, 2000, [1999 - 100 * b for b in range(19)]),
 ]
 
 
