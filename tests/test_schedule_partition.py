@@ -7,8 +7,11 @@ workgroup whose range meets the slab (ceil((Ps+1)*G/Ru) - 1), with Ru < G by
 the unit's index in the slab (ranges then hold at most one unit; empty
 ranges take no slot).  These closed forms must give every unit to exactly
 one workgroup and each slab the slots 0..count-1, with count at most
-min(G, units + 1) -- the bound the workspace is sized by.  Brute force over
-random length mixes checks that.
+min(G, units + 1) -- the bound the workspace is sized by.  Where a slab has
+more units than its J slots and more workgroups could meet it than those, only
+as many take part as keep it within them (the chunk kernels cut the space of
+their (sequence, query tile, KV head) items by the same rule).  Brute force
+over random length mixes checks that.
 """
 import random
 
@@ -67,6 +70,49 @@ def test_static_ranges_cover_once_and_slots_are_dense(seed):
             count = static_visits(P[s], st, Ru, G)
             assert sorted(slots.get(s, [])) == list(range(count))
             assert count <= min(G, st + 1)
+
+
+def workgroups_taking_part(units, G, J):
+    """The kernels' cap, from what they know: the units of all slabs and the
+    most that any slab has."""
+    most = max(units)
+    return G if most <= J else max(1, min(G, sum(units) * (J - 2) // most))
+
+
+@pytest.mark.parametrize("seed", range(6))
+def test_visits_stay_within_the_slots(seed):
+    rng = random.Random(200 + seed)
+    capped = 0
+    for _ in range(400):
+        G = rng.choice([1, 2, 3, 7, 64, 88, 256, 512])
+        if rng.random() < 0.5:                        # slabs, several of each sequence
+            per_b = rng.choice([1, 2, 8])
+            units = [u for _ in range(rng.randint(1, 12))
+                     for u in [rng.choice([0, 1, 2, rng.randint(0, 300)])] * per_b]
+        else:                                         # causal query tiles x KV heads
+            units = []
+            for _ in range(rng.randint(1, 5)):
+                n, tiles, heads = rng.randint(0, 200), rng.randint(1, 6), rng.choice([1, 2, 8])
+                for t in range(tiles):
+                    units += [n + rng.randint(0, 4) * t] * heads
+        if sum(units) == 0:
+            continue
+        J = rng.choice([3, 3, 4, 5, 17, rng.randint(3, 120)])
+        Gw = workgroups_taking_part(units, G, J)
+        capped += Gw < G
+        P, Ru, visits = visits_and_slots(units, Gw)
+        cover = [0] * Ru
+        slots = {}
+        for _, s, rows, slot in visits:
+            for x in rows:
+                cover[x] += 1
+            slots.setdefault(s, []).append(slot)
+        assert all(c == 1 for c in cover)
+        for s, st in enumerate(units):
+            count = static_visits(P[s], st, Ru, Gw)
+            assert count <= J, (units, G, J)
+            assert sorted(slots.get(s, [])) == list(range(count))
+    assert capped > 50
 
 
 def test_one_slab_holding_everything_uses_every_workgroup():
