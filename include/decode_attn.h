@@ -95,7 +95,8 @@ const char *da_status_string(da_status status);
  * Bytes of device workspace da_decode_attn, da_decode_step and the
  * da_decode_partial + da_decode_merge pair need for these shapes (the
  * library chooses its work decomposition; the size covers every device the
- * library runs on).  Returns 0 if the shapes are invalid.
+ * library runs on; for caches of n_max <= 768 rows it also covers every smaller
+ * B).  Returns 0 if the shapes are invalid.
  */
 size_t da_decode_workspace_bytes(int B, int h_q, int h_kv, int n_max, int d_k,
                                  int d_v);
@@ -148,8 +149,11 @@ da_status da_decode_workspace_reset(void *workspace, size_t workspace_bytes,
  * every slab is a single segment (n_max <= 768, or at least 2048 (b, KV
  * head) slabs with n_max <= 4608, h_q / h_kv <= 16 and d_k + d_v <= 256) the
  * decode is a single launch that writes out directly, unless the slabs are
- * few and long enough to be split (at most 64, n_max * (d_k + d_v) >=
- * 131072).  Equivalent to da_decode_partial followed by da_decode_merge.
+ * few and long enough to be split (n_max <= 768, at most 64 slabs of 32 query
+ * rows, n_max * (d_k + d_v) >= 131072) and the workspace is of the size that
+ * da_decode_workspace_bytes names; such a call also runs, unsplit, in the
+ * smaller workspace that da_decode_workspace_bytes_ex names for its segment
+ * rows.  Equivalent to da_decode_partial followed by da_decode_merge.
  *
  * Supported: d_k, d_v in {64, 128, 256}; any B, h_q, h_kv >= 1 with h_kv | h_q.
  * workspace: see above; at least da_decode_workspace_bytes(...) bytes,
@@ -171,9 +175,9 @@ da_status da_decode_attn(const float *q, const float *K, const float *V,
  * launch reads the new row of each KV head straight from k_new / v_new (and
  * writes it into the cache meanwhile), and the merge advances len.  When
  * every slab is short (n_max within one segment, and not split: see above),
- * h_q / h_kv <= 16 and d_k + d_v <= 256, the whole step is one launch: one workgroup per
- * (b, KV head, head group) writes its output rows, and the last workgroup of
- * each sequence to finish advances len[b].  Same results, same argument
+ * h_q / h_kv <= 16 and d_k + d_v <= 256, the whole step is one launch: one
+ * workgroup per (b, KV head, head group) writes its output rows, and the last
+ * workgroup of each sequence to finish advances len[b].  Same results, same argument
  * rules as the two calls; k_new [B][h_kv][d_k] and v_new [B][h_kv][d_v] must
  * not overlap K / V.
  */

@@ -2612,17 +2612,20 @@ void refine_grid(int n_max, int resident, Plan* plan) {
 
 // The plan of a call: plan_chunks', refined where the library chooses the
 // segment size.  (The partials' layout depends on the slots J alone, which the
-// grid's refinement leaves as they are, so every call with the same shapes and
-// chunk_rows agrees on it.)
+// grid's refinement leaves as they are, so every call with the same shapes
+// agrees on it.)  Single-segment slabs are split only if `have`, the bytes of
+// the caller's workspace, holds the split plan's slots as well: a workspace
+// sized for the direct form goes on serving, in that form.  0 for the halves
+// of a decode that are called apart, which need not be told the same size or
+// segment rows.
 da_status make_plan(int B, int h_q, int h_kv, int n_max, int d_k, int d_v, int chunk_rows,
-                    int resident, Plan* plan) {
+                    size_t have, int resident, Plan* plan) {
   const da_status st = plan_chunks(B, h_q, h_kv, n_max, d_k, d_v, chunk_rows, resident, plan);
   if (st != DA_OK || chunk_rows != 0 || B > kMaxStaticSeqs) return st;
   if (!plan->single_chunk) {
     if (plan->fnum == kStaticDen) refine_grid(n_max, resident, plan);
   } else if (plan->slabs <= kSplitMaxSlabs && (int64_t)n_max * (d_k + d_v) >= kSplitMinFloats) {
-    // A slot for every kMinRangeRows rows; the library's own workspace goes on
-    // holding what it held.
+    // A slot for every kMinRangeRows rows.
     Plan split = *plan;
     split.single_chunk = false;
     split.two_waves = plan->blocks == 1 && d_k + d_v <= 256;
@@ -2633,9 +2636,26 @@ da_status make_plan(int B, int h_q, int h_kv, int n_max, int d_k, int d_v, int c
     split.J = (int)ceil_div(n_max, kMinRangeRows) + 2;
     refine_grid(n_max, resident, &split);
     size_plan(B, h_q, d_v, &split);
-    if (split.bytes <= kScratchBytes) *plan = split;
+    if (split.bytes <= have) *plan = split;
   }
   return DA_OK;
+}
+
+// The workspace that calls of these shapes make use of.  A batch of more slabs
+// than are split may hold fewer bytes per sequence than a smaller one that is:
+// its size covers that one too, so that a workspace sized for a program's
+// largest batch serves the smaller ones as their own would.
+size_t plan_bytes(int B, int h_q, int h_kv, int n_max, int d_k, int d_v, int chunk_rows) {
+  Plan pl;
+  if (make_plan(B, h_q, h_kv, n_max, d_k, d_v, chunk_rows, SIZE_MAX, kMaxResident, &pl) != DA_OK)
+    return 0;
+  if (chunk_rows != 0 || n_max > kDefaultChunkRows) return pl.bytes;
+  const int fewer = std::min(B, kSplitMaxSlabs / (pl.slabs / B));
+  Plan small;
+  if (fewer < 1 || make_plan(fewer, h_q, h_kv, n_max, d_k, d_v, 0, SIZE_MAX, kMaxResident,
+                             &small) != DA_OK)
+    return pl.bytes;
+  return std::max(pl.bytes, small.bytes);
 }
 
 struct WsView {
@@ -2798,7 +2818,8 @@ da_status partial_impl(const float* q, const float* K, const float* V, const flo
   // Validated against the documented size (the plan for kMaxResident), run
   // with the device's own plan (never larger).
   Plan pl;
-  da_status st = make_plan(B, rows, h_kv, n_max, d_k, d_v, chunk_rows, kMaxResident, &pl);
+  const size_t have = allow_direct ? workspace_bytes : 0;
+  da_status st = make_plan(B, rows, h_kv, n_max, d_k, d_v, chunk_rows, have, kMaxResident, &pl);
   if (st != DA_OK) return st;
   if (!aligned(q, 16) || !aligned(K, 16) || !aligned(V, 16) || !aligned(len, 4) ||
       !aligned(k_new, 16) || !aligned(v_new, 16) || !aligned(out, 16))
@@ -2806,7 +2827,7 @@ da_status partial_impl(const float* q, const float* K, const float* V, const flo
   if (!std::isfinite(scale)) return DA_ERR_SCALE;
   if (!workspace || workspace_bytes < pl.bytes) return DA_ERR_WORKSPACE;
   if (!aligned(workspace, 16)) return DA_ERR_ALIGN;
-  (void)make_plan(B, rows, h_kv, n_max, d_k, d_v, chunk_rows, device_resident(), &pl);
+  (void)make_plan(B, rows, h_kv, n_max, d_k, d_v, chunk_rows, have, device_resident(), &pl);
   if (out_plan) *out_plan = pl;
 
   const WsView w = view(pl, workspace);
@@ -2856,17 +2877,18 @@ da_status partial_impl(const float* q, const float* K, const float* V, const flo
 
 da_status merge_impl(float* out, int32_t* len_bump, int B, int h_q, int h_kv, int n_max,
                      int d_k, int d_v, int T, int chunk_rows, void* workspace,
-                     size_t workspace_bytes, void* stream) {
+                     size_t workspace_bytes, void* stream, bool whole = false) {
   if (!out) return DA_ERR_NULL;
   const int rows = query_rows(h_q, T);
   if (rows < 0 || h_q < 1) return DA_ERR_SHAPE;
   Plan pl;
-  da_status st = make_plan(B, rows, h_kv, n_max, d_k, d_v, chunk_rows, kMaxResident, &pl);
+  const size_t have = whole ? workspace_bytes : 0;
+  da_status st = make_plan(B, rows, h_kv, n_max, d_k, d_v, chunk_rows, have, kMaxResident, &pl);
   if (st != DA_OK) return st;
   if (!aligned(out, 16) || !aligned(len_bump, 4)) return DA_ERR_ALIGN;
   if (!workspace || workspace_bytes < pl.bytes) return DA_ERR_WORKSPACE;
   if (!aligned(workspace, 16)) return DA_ERR_ALIGN;
-  (void)make_plan(B, rows, h_kv, n_max, d_k, d_v, chunk_rows, device_resident(), &pl);
+  (void)make_plan(B, rows, h_kv, n_max, d_k, d_v, chunk_rows, have, device_resident(), &pl);
 
   const WsView w = view(pl, workspace);
   hipStream_t s = static_cast<hipStream_t>(stream);
@@ -2954,7 +2976,7 @@ size_t da_decode_workspace_bytes(int B, int h_q, int h_kv, int n_max, int d_k, i
 size_t da_decode_workspace_counter_bytes(int B, int h_q, int h_kv, int n_max, int d_k,
                                          int d_v) {
   Plan pl;
-  if (make_plan(B, h_q, h_kv, n_max, d_k, d_v, 0, kMaxResident, &pl) != DA_OK) return 0;
+  if (make_plan(B, h_q, h_kv, n_max, d_k, d_v, 0, 0, kMaxResident, &pl) != DA_OK) return 0;
   return pl.counter_bytes;
 }
 
@@ -2962,7 +2984,7 @@ da_status da_decode_workspace_reset(void* workspace, size_t workspace_bytes, int
                                     int h_kv, int n_max, int d_k, int d_v, void* stream) {
   if (!workspace) return DA_ERR_NULL;
   Plan pl;
-  const da_status st = make_plan(B, h_q, h_kv, n_max, d_k, d_v, 0, kMaxResident, &pl);
+  const da_status st = make_plan(B, h_q, h_kv, n_max, d_k, d_v, 0, 0, kMaxResident, &pl);
   if (st != DA_OK) return st;
   if (workspace_bytes < pl.counter_bytes) return DA_ERR_WORKSPACE;
   if (!aligned(workspace, 16)) return DA_ERR_ALIGN;
@@ -3020,7 +3042,7 @@ da_status da_decode_multi_step(const float* q, float* K, float* V, const float* 
   // The chunk kernels or the direct form did the whole step.
   if (pl.chunked || direct_two_waves(pl, d_k, d_v)) return DA_OK;
   return merge_impl(out, len, B, h_q, h_kv, n_max, d_k, d_v, T, 0, workspace,
-                    workspace_bytes, stream);
+                    workspace_bytes, stream, true);
 }
 
 da_status da_kv_append_rows(float* K, float* V, const float* k_new, const float* v_new,
@@ -3064,16 +3086,13 @@ da_status da_kv_append(float* K, float* V, const float* k_new, const float* v_ne
 
 int da_decode_chunk_rows(int B, int h_q, int h_kv, int n_max, int d_k, int d_v) {
   Plan pl;
-  if (make_plan(B, h_q, h_kv, n_max, d_k, d_v, 0, kMaxResident, &pl) != DA_OK) return 0;
+  if (make_plan(B, h_q, h_kv, n_max, d_k, d_v, 0, 0, kMaxResident, &pl) != DA_OK) return 0;
   return pl.chunk_rows;
 }
 
 size_t da_decode_workspace_bytes_ex(int B, int h_q, int h_kv, int n_max, int d_k, int d_v,
                                     int chunk_rows) {
-  Plan pl;
-  if (make_plan(B, h_q, h_kv, n_max, d_k, d_v, chunk_rows, kMaxResident, &pl) != DA_OK)
-    return 0;
-  return pl.bytes;
+  return plan_bytes(B, h_q, h_kv, n_max, d_k, d_v, chunk_rows);
 }
 
 da_status da_decode_multi_ex(const float* q, const float* K, const float* V,
@@ -3087,7 +3106,7 @@ da_status da_decode_multi_ex(const float* q, const float* K, const float* V,
   if (st != DA_OK) return st;
   if (pl.chunked || pl.single_chunk) return DA_OK;    // the chunk kernels or the direct form
   return merge_impl(out, nullptr, B, h_q, h_kv, n_max, d_k, d_v, T, chunk_rows, workspace,
-                    workspace_bytes, stream);
+                    workspace_bytes, stream, true);
 }
 
 da_status da_decode_partial_ex(const float* q, float* K, float* V, const float* k_new,
@@ -3113,7 +3132,7 @@ da_status da_decode_attn_noalloc(const float* q, const float* K, const float* V,
                                  int h_kv, int n_max, int d_k, int d_v, void* stream) {
   if (!q || !K || !V || !len || !out) return DA_ERR_NULL;
   Plan pl;
-  da_status st = make_plan(B, h_q, h_kv, n_max, d_k, d_v, 0, kMaxResident, &pl);
+  da_status st = make_plan(B, h_q, h_kv, n_max, d_k, d_v, 0, 0, kMaxResident, &pl);
   if (st != DA_OK) return st;
   if (pl.bytes > kScratchBytes) return DA_ERR_WORKSPACE;
   if (!aligned(q, 16) || !aligned(K, 16) || !aligned(V, 16) || !aligned(len, 4) ||

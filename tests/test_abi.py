@@ -127,6 +127,25 @@ def _expected_workspace(B, h_q, h_kv, n_max, d_k, d_v, c):
     return counters, counters + pad(slots * 8) + slots * d_v * 4
 
 
+def expected_bytes(B, h_q, h_kv, n_max, d_k, d_v):
+    """The size the library reports: caches of one segment of which a batch
+    holds at most 64 slabs of at least 131072 values are split, with a slot for
+    every 128 rows and two more; a larger batch's size is no smaller than that
+    of the largest one that is split."""
+    total = _expected_workspace(B, h_q, h_kv, n_max, d_k, d_v,
+                                expected_chunk_rows(B, h_q, h_kv, n_max, d_k, d_v))[1]
+    if n_max > 768 or n_max * (d_k + d_v) < 131072:
+        return total
+    pad = lambda x: -(-x // 256) * 256
+    per_seq = h_kv * -(-(h_q // h_kv) // 32)
+    fewer = min(B, 64 // per_seq)
+    if fewer < 1:
+        return total
+    slots = fewer * h_q * (-(-n_max // 128) + 2)
+    counters = pad(fewer * per_seq * 128) + pad(fewer * h_q * 4)
+    return max(total, counters + pad(slots * 8) + slots * d_v * 4)
+
+
 def expected_chunk_rows(B, h_q, h_kv, n_max, d_k, d_v):
     """The library's segment size: 768 rows, or the whole cache rounded up to
     768 if shorter, or if there are at least 2048 slabs of at most 4608 rows
@@ -151,10 +170,15 @@ def test_chunk_rows_and_workspace_sizes():
                  (512, 8, 4, 2000, 128, 256), (128, 32, 8, 8192, 128, 128),
                  (256, 16, 4, 2048, 64, 64), (1024, 8, 1, 5000, 128, 128),
                  (2, 32, 8, 32768, 128, 128), (1, 32, 8, 65536, 128, 128),
-                 (4, 32, 8, 16384, 64, 64), (16, 16, 4, 16384, 128, 128)]:
+                 (4, 32, 8, 16384, 64, 64), (16, 16, 4, 16384, 128, 128),
+                 (8, 32, 8, 768, 128, 128), (9, 32, 8, 768, 128, 128),
+                 (16, 32, 8, 768, 128, 128), (300, 32, 8, 768, 128, 128),
+                 (1, 4, 1, 512, 128, 128), (1, 4, 1, 511, 128, 128),
+                 (2, 32, 1, 700, 128, 128), (1, 4, 2, 256, 256, 256),
+                 (1, 4096, 8, 700, 128, 128), (1, 130, 65, 700, 128, 128)]:
         c = binding.chunk_rows(*args)
         assert c == expected_chunk_rows(*args), args
-        counters, total = _expected_workspace(*args, c)
+        counters, total = _expected_workspace(*args, c)[0], expected_bytes(*args)
         assert binding.workspace_counter_bytes(*args) == counters
         assert binding.workspace_bytes(*args) == total
         assert lib.da_decode_workspace_bytes(*args) == total
@@ -165,6 +189,36 @@ def test_chunk_rows_and_workspace_sizes():
     assert binding.workspace_bytes(1, 1, 1, 10, 64, 64, 192) == 0  # chunk not a multiple of 768
     assert binding.workspace_bytes(1, 1, 1, 10, 64, 64, 384) == 0
     assert lib.da_decode_workspace_bytes(1, 3, 2, 10, 64, 64) == 0
+
+
+def _takes(B, h_q, h_kv, n_max, d_k, d_v, size, T=1):
+    """Whether a call takes a workspace of that many bytes: its alignment is
+    checked after its size, so nothing is launched."""
+    head = (FAKE, FAKE, FAKE, FAKE, 0.125, FAKE, B, h_q // T, h_kv, n_max, d_k, d_v)
+    status = lib.da_decode_multi_ex(*head, T, 0, FAKE + 4, size, None)
+    assert status in (4, 6)
+    return status == 4
+
+
+def test_workspaces_of_split_slabs():
+    """A program that sizes its workspace once, for its largest batch, or for the
+    form that is not split, is served at every smaller batch; the halves of a
+    decode that are called apart never split."""
+    for h_q, h_kv, n_max, d in ((32, 8, 768, 128), (16, 16, 600, 128), (8, 1, 300, 256),
+                                (32, 1, 700, 128), (160, 1, 700, 128)):
+        sizes = [binding.workspace_bytes(B, h_q, h_kv, n_max, d, d) for B in range(1, 100)]
+        assert sizes == sorted(sizes)
+        for B in range(1, 100):
+            direct = _expected_workspace(B, h_q, h_kv, n_max, d, d, 768)[1]
+            assert _takes(B, h_q, h_kv, n_max, d, d, direct)
+            assert not _takes(B, h_q, h_kv, n_max, d, d, direct - 1)
+            assert _takes(B, h_q, h_kv, n_max, d, d, sizes[-1])
+            if h_q // 4 % h_kv == 0:
+                assert _takes(B, h_q, h_kv, n_max, d, d, direct, T=4)
+            halves = (FAKE, FAKE, FAKE, None, None, FAKE, 0.1, B, h_q, h_kv, n_max, d, d)
+            assert lib.da_decode_partial(*halves, FAKE + 4, direct, None) == 4
+            assert lib.da_decode_merge(FAKE, None, B, h_q, h_kv, n_max, d, d, FAKE + 4, direct,
+                                       None) == 4
 
 
 @pytest.mark.parametrize("value", ["0", "32", "1000", "bad", ""])

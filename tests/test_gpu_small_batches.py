@@ -59,3 +59,40 @@ def test_small_batches(cuda_device, schedule, shape):
     assert np.max(np.abs(step.cpu().numpy() - ref)) <= 1e-5
     assert ln.tolist() == inp.lens.tolist()
     assert np.array_equal(K.cpu().numpy().view(np.uint32), inp.K.view(np.uint32))
+
+
+@pytest.mark.parametrize("shape", [SHAPES[0], SHAPES[2], SHAPES[4], SHAPES[5]], ids=str)
+def test_split_slabs_on_less_workspace(cuda_device, shape):
+    """Slabs that are split where the workspace holds the slots: in one of the
+    direct form's size, whole calls and the two halves, which may name the
+    library's segment rows in one and leave them to it in the other."""
+    B, h_q, h_kv, d_k, d_v, n_max, lens = shape
+    sh = workloads.custom("small", B=B, h_q=h_q, h_kv=h_kv, d_k=d_k, d_v=d_v, n_max=n_max, steps=1)
+    inp = workloads.make(sh, seed=11, lens=np.array(lens, np.int32))
+    dev = lambda x: torch.from_numpy(np.ascontiguousarray(x)).to(cuda_device)  # noqa: E731
+    q, K, V, ln = dev(inp.q), dev(inp.K), dev(inp.V), dev(inp.lens)
+    sc = float(sh.scale32())
+    rows = binding.chunk_rows(B, h_q, h_kv, n_max, d_k, d_v)
+    size = binding.workspace_bytes(B, h_q, h_kv, n_max, d_k, d_v, rows)
+    assert size < binding.workspace_bytes(B, h_q, h_kv, n_max, d_k, d_v)
+    nc = binding.workspace_counter_bytes(B, h_q, h_kv, n_max, d_k, d_v)
+    full = torch.full((size + 4096,), 0xFF, dtype=torch.uint8, device=cuda_device)
+    ws = full[:size]
+    ws[:nc].zero_()
+    ref = oracle.decode(inp.q, inp.K, inp.V, inp.lens, sh.scale32())
+    print("less workspace", shape, flush=True)
+    outs = [binding.decode_attn(q, K, V, ln, sc, workspace=ws)]
+    for first, second in ((0, rows), (rows, 0), (0, 0)):
+        binding.decode_partial(q, K, V, ln, sc, ws, first)
+        outs.append(binding.decode_merge(torch.empty_like(outs[0]), ws, B, h_q, h_kv, n_max, d_k,
+                                         d_v, second))
+    step = binding.decode_step(dev(inp.q_step[0]), K, V, dev(inp.k_new[0]), dev(inp.v_new[0]), ln,
+                               sc, workspace=ws)
+    torch.cuda.synchronize()
+    assert not ws[:nc].any() and bool((full[size:] == 0xFF).all())
+    for out in outs:
+        assert np.max(np.abs(out.cpu().numpy() - ref)) <= 1e-5
+    oracle.append(inp.K, inp.V, inp.k_new[0], inp.v_new[0], inp.lens)
+    ref = oracle.decode(inp.q_step[0], inp.K, inp.V, inp.lens, sh.scale32())
+    assert np.max(np.abs(step.cpu().numpy() - ref)) <= 1e-5
+    assert ln.tolist() == inp.lens.tolist()
