@@ -139,9 +139,9 @@ constexpr int kMaxSlabVisitors = 128;
 // workgroup per slab would leave most of the chip idle: at most
 // kSplitMaxSlabs slabs of at least kSplitMinFloats values (512 rows at d =
 // 128).  The merge launch costs what the shorter reads save near that line
-// (steps of 32/8 heads, d = 128, direct form / split: 8 slabs x 700 rows 22.3
-// / 17.9 us, 64 x 765 23.8 / 21.1, 64 x 509 18.9 / 17.6, 4 x 381 15.8 / 17.6,
-// 128 x 765 24.7 / 28.9; 8 slabs x 700 rows at d = 256 44.5 / 20.4).
+// (steps of 32/8 heads, d = 128, direct form / split: 8 slabs x 700 rows 23.1
+// / 15.2 us, 64 x 765 24.2 / 19.6, 64 x 509 18.8 / 18.8, 4 x 381 15.8 / 17.6,
+// 128 x 765 24.7 / 28.9; 8 slabs x 700 rows at d = 256 52.0 / 22.6).
 constexpr int kSplitMaxSlabs = 64;
 constexpr int64_t kSplitMinFloats = 131072;
 // The workspace that the library holds itself (da_decode_attn_noalloc).
@@ -836,8 +836,9 @@ __device__ __forceinline__ void process_tile(const Tile<DK, DV, NB>& T, int row0
 // Rows are scheduled in units of Cd rows (one turn of the tile ring for all
 // four waves).  Every slab of sequence b holds st(b) = floor(fnum/16 * n_b /
 // Cd) static units at its start (ceil(n_b / Cd), all of it, for fnum = 16);
-// the rest of its rows is its dynamic part, handed out one unit at a time.  The static units of all slabs, in slab
-// order, form one space of Ru units that is cut into gridDim.x contiguous
+// the rest of its rows is its dynamic part, handed out one unit at a time.
+// The static units of all slabs, in slab order, form one space of Ru units
+// that is cut into gridDim.x contiguous
 // ranges, [w*Ru/G, (w+1)*Ru/G) for workgroup w: the ranges are proportional
 // to the rows, so every workgroup starts with the same amount of work (to
 // one unit) and without touching a counter.  A range covers one or more
@@ -1702,11 +1703,11 @@ __global__ __launch_bounds__(kThreads) void decode_merge_kernel(
 //
 // Bound by the matrix cores and what of the waves' other work finds no partner
 // there: 2 sequences x 32/8 heads x 512 rows behind 1000-7600 keys, d = 128 (86
-// GFLOP; 210 us at the 16-bit rate with six products for one): 452 us, with
-// fp32 products in groups of 32 rows 942, with two-term fp16 sums 307.  The
-// matrix cores are busy 55 % of the time, the vector units 29 %; without
-// loads and staging it takes 430 us, and neither reading operands further
-// ahead, wave priorities, nor more loads in flight change it by more than 3 %.
+// GFLOP; 210 us at the 16-bit rate with six products for one): 421 us, with
+// fp32 products in groups of 32 rows 937, with two-term fp16 sums 284.  The
+// matrix cores are busy 60 % of the time, the vector units 31 %; without loads
+// and staging it takes 14 % less, and neither reading operands further ahead,
+// wave priorities, nor more loads in flight change it by more than 3 %.
 // Prompt of 1500 rows x 16 heads, d = 64: 64 us from 237.  A key of NaN adds 4
 // % to the first (its tile is formed apart); values of 2^59 and
 // above throughout make it 2.5 ms.
