@@ -234,8 +234,8 @@ da_status da_decode_merge(float *out, int32_t *len, int B, int h_q, int h_kv,
  * da_decode_workspace_bytes(B, h_q*T, h_kv, ...) bytes, its counter region
  * da_decode_workspace_counter_bytes(B, h_q*T, h_kv, ...).  T <= 4096.  Other
  * rules as da_decode_attn.  Rows of V that a query row does not see have weight
- * 0 in it: they must be finite, as 0 * inf is NaN (the kernels for many query
- * rows leave them out, the others do not).
+ * 0 in it: with up to 32 query rows per KV head they must be finite, as 0 * inf
+ * is NaN; larger steps leave them out.
  */
 da_status da_decode_multi(const float *q, const float *K, const float *V,
                           const int32_t *len, float scale, float *out, int B,

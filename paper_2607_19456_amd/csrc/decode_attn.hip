@@ -658,15 +658,33 @@ __device__ __forceinline__ void process_tile_pairs(const Tile<DK, DV, NB>& T, in
     }
 }
 
+// Causal columns: an infinite value or NaN of a row that not all columns see
+// (rows > all_see) must not reach those that don't, where its weight is 0 (0 *
+// inf is NaN).  Such values are taken out of the tile (noted in `left_out`) and
+// added at the visit's end to the columns that do see them.  Whole steps of
+// more than 32 query rows per KV head, which share this with the chunk kernels;
+// it costs them 5 % (160 shapes of 1-64 slabs x 200-30000 rows; 8 % at most,
+// and more anywhere else in the tile), and the others go without.
+__device__ __forceinline__ void leave_out(f4& v, bool& left_out) {
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const bool bad = !(fabsf(v[e]) < INFINITY);
+    left_out = left_out || bad;
+    if (bad) v[e] = 0.f;
+  }
+}
+
 // One 16-row tile for NB column blocks of query heads: scores on the matrix
 // cores, online softmax update, weighted-sum update on the matrix cores.
-template <int DK, int DV, int NB, bool CAUSAL, bool PINQ>
-__device__ __forceinline__ void process_tile(const Tile<DK, DV, NB>& T, int row0,
+template <int DK, int DV, int NB, bool CAUSAL, bool PINQ, bool HIDES>
+__device__ __forceinline__ void process_tile(Tile<DK, DV, NB>& T, int row0,
                                              const int (&lim)[NB], int k, int lane,
                                              const f4 (*__restrict__ sh_q)[DK / 16][kWave],
                                              const f4 (&qr)[NB][DK / 16],
                                              float (&m_run)[NB], float (&l_run)[NB],
-                                             f4 (&acc)[NB][DV / 64][4]) {
+                                             f4 (&acc)[NB][DV / 64][4], int all_see,
+                                             bool& left_out) {
+  static_assert(!HIDES || (CAUSAL && NB == 2), "the instances that take many query rows");
   // Unpinned, q is re-read from LDS for every tile: the empty asm keeps the
   // compiler from hoisting those reads out of the tile loop.
   if constexpr (!PINQ) asm volatile("" ::: "memory");
@@ -745,6 +763,15 @@ __device__ __forceinline__ void process_tile(const Tile<DK, DV, NB>& T, int row0
       pr[nb][2] = fast_exp2(sc[nb][2] - m_ref);
       pr[nb][3] = fast_exp2(sc[nb][3] - m_ref);
       l_run[nb] += (pr[nb][0] + pr[nb][1]) + (pr[nb][2] + pr[nb][3]);
+    }
+    if constexpr (HIDES) {
+      if (row0 + kTileRows - 1 > all_see) {
+#pragma unroll
+        for (int rho = 0; rho < 4; ++rho)
+          if (row0 + 4 * k + rho > all_see)
+#pragma unroll
+            for (int c = 0; c < DV / 64; ++c) leave_out(T.v[rho][c], left_out);
+      }
     }
 #pragma unroll
     for (int rho = 0; rho < 4; ++rho)
@@ -1003,7 +1030,8 @@ __device__ int find_open_slab(const unsigned* __restrict__ cnt,
 //   ws_ml      [B][h_q][J] float2        (reference, base-2 units; sum)
 //   ws_acc     [B][h_q][J][DV]           unnormalised weighted sum of V rows
 // ---------------------------------------------------------------------------
-template <int DK, int DV, int NB, bool CAUSAL, int W>
+// HIDES: see leave_out.
+template <int DK, int DV, int NB, bool CAUSAL, int W, bool HIDES = false>
 __global__ __launch_bounds__(kThreads, W) void decode_partial_kernel(
     const float* __restrict__ q, float* __restrict__ K,
     float* __restrict__ V, const float* __restrict__ k_new,
@@ -1251,6 +1279,8 @@ __global__ __launch_bounds__(kThreads, W) void decode_partial_kernel(
     // pos0 = len[b] before a fused append (the rows of one step enter one per
     // position), else n - T (the last T positions of the cache).
     int lim[NB];
+    const int all_see = !CAUSAL ? last_row : app ? (int)len_b : n - T;
+    bool left_out = false;
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) {
       lim[nb] = last_row;
@@ -1405,8 +1435,8 @@ __global__ __launch_bounds__(kThreads, W) void decode_partial_kernel(
                                                              sh_k[PAIRS ? wave : 0], sh_q, qr,
                                                              m_run, l_run, acc);
               else
-                process_tile<DK, DV, NB, CAUSAL, kPin>(ring[p], r, lim, k, lane, sh_q, qr, m_run,
-                                                       l_run, acc);
+                process_tile<DK, DV, NB, CAUSAL, kPin, HIDES>(
+                    ring[p], r, lim, k, lane, sh_q, qr, m_run, l_run, acc, all_see, left_out);
             }
           }
           t += R;
@@ -1432,6 +1462,29 @@ __global__ __launch_bounds__(kThreads, W) void decode_partial_kernel(
         } else {
           ns = req ? dyn_row(sh_next[it & 1]) : -1;
           ntpw = tpw_d;
+        }
+      }
+    }
+
+    if constexpr (HIDES) {
+      if (__any(left_out)) {
+#pragma unroll 1
+        for (int key = max(all_see, -1) + 1; key <= last_row; ++key) {
+          const float* vr = (unsigned)(key - src.new_lo) < (unsigned)src.new_cnt
+                                ? src.v_new_rows + (int64_t)(key - src.new_lo) * DV
+                                : src.Vs + (int64_t)key * DV;
+#pragma unroll
+          for (int nb = 0; nb < NB; ++nb)
+            if (key <= lim[nb] && m_run[nb] != -INFINITY)
+#pragma unroll
+              for (int cc = 0; cc < DV / 64; ++cc)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                  const f4 v = load4(vr + 64 * cc + 16 * k + 4 * r);
+#pragma unroll
+                  for (int e = 0; e < 4; ++e)
+                    if (!(fabsf(v[e]) < INFINITY)) acc[nb][cc][e][r] += v[e];
+                }
         }
       }
     }
@@ -1497,7 +1550,8 @@ __global__ __launch_bounds__(kThreads, W) void decode_partial_kernel(
           } else {
             dst = ws_acc + slot * DV;
             if (k == 0) {
-              ws_ml[slot] = make_float2(M, L);
+              // (A row whose scores are all NaN has no reference, but counts.)
+              ws_ml[slot] = make_float2(HIDES && L != L ? M_ref : M, L);
               atomicAdd(nvis + head, 1u);
             }
           }
@@ -2692,6 +2746,7 @@ struct PartialArgs {
   int T;                     // query rows per head (1: single-query decode)
   float* out_direct;         // set: single-chunk slabs, output written directly
   int32_t* len_bump;         // direct form of a fused append: len, advanced in the kernel
+  bool hides;                // infinities and NaN reach only the rows that see them
 };
 
 // The direct form runs two waves per SIMD for one column block and
@@ -2717,11 +2772,19 @@ void launch_partial(const Plan& pl, const PartialArgs& a, const WsView& w, hipSt
       return;
     }
   }
-  hipLaunchKernelGGL((decode_partial_kernel<DK, DV, NB, CAUSAL, 1>), dim3(grid), dim3(kThreads),
-                     0, stream, a.q, a.K, a.V, a.k_new, a.v_new, a.len, a.qscale, a.B, a.h_q,
-                     a.h_kv, a.n_max, a.T, pl.chunk_rows, pl.dyn_rows,
-                     a.out_direct ? 0 : pl.fnum, pl.head_groups, pl.J, pl.Jd, w.cnt, w.nvis,
-                     w.ml, w.acc, a.out_direct, a.len_bump);
+  auto launch = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3(grid), dim3(kThreads), 0, stream, a.q, a.K, a.V, a.k_new,
+                       a.v_new, a.len, a.qscale, a.B, a.h_q, a.h_kv, a.n_max, a.T, pl.chunk_rows,
+                       pl.dyn_rows, a.out_direct ? 0 : pl.fnum, pl.head_groups, pl.J, pl.Jd, w.cnt,
+                       w.nvis, w.ml, w.acc, a.out_direct, a.len_bump);
+  };
+  if constexpr (NB == 2 && CAUSAL) {
+    if (a.hides) {
+      launch(decode_partial_kernel<DK, DV, NB, CAUSAL, 1, true>);
+      return;
+    }
+  }
+  launch(decode_partial_kernel<DK, DV, NB, CAUSAL, 1>);
 }
 
 template <int DK, int DV>
@@ -2841,7 +2904,8 @@ da_status partial_impl(const float* q, const float* K, const float* V, const flo
                       : nullptr;
   int32_t* bump = direct && k_new ? const_cast<int32_t*>(len) : nullptr;
   const PartialArgs a{q, const_cast<float*>(K), const_cast<float*>(V), k_new, v_new, len,
-                      scale * kLog2e, B, rows, h_kv, n_max, T, direct, bump};
+                      scale * kLog2e, B, rows, h_kv, n_max, T, direct, bump,
+                      allow_direct && chunk_rows == 0 && T > 1 && pl.head_groups > 1};
   hipStream_t s = static_cast<hipStream_t>(stream);
   (void)hipGetLastError();
   if (allow_direct && chunk_rows == 0 && T > 1 &&

@@ -3,7 +3,7 @@ edges of the query tiles and key tiles, every pair of head sizes, ragged,
 empty and clipped lengths, items cut over many workgroups and items that may
 not be cut, and values that need care as 16-bit operands: magnitudes far from
 1, growing and falling ones, infinities and NaN.  The small shapes stay with
-the decode kernels; the ones after them, and BASE, take the chunk kernels.
+the decode kernels; the ones after them take the chunk kernels.
 
 Tolerance: 1e-5 of V's largest magnitude, as for the other decodes at N(0, 1)
 (values of about 4: the fp32 sums of at most a few thousand terms and the
@@ -124,7 +124,20 @@ def test_chunk_shapes(cuda_device, shape):
     run_both(*shape)
 
 
-BASE = (32, 4, 1, 128, 128, 800, 40, [500] * 32)
+# The same step where the decode kernels take it and where the chunk kernels do.
+BASE = {"decode": (1, 4, 1, 128, 128, 600, 40, [500]),
+        "chunk": (32, 4, 1, 128, 128, 800, 40, [500] * 32)}
+# For what must stay with the rows that see it: other sizes, the direct form.
+MORE = {"decode_64": (2, 4, 1, 64, 64, 900, 40, [500] * 2),
+        "decode_256": (1, 4, 1, 256, 256, 600, 40, [500]),
+        "decode_64_256": (1, 4, 1, 64, 256, 600, 40, [500]),
+        "decode_direct": (60, 4, 1, 64, 64, 600, 40, [500] * 60),
+        "chunk_256": (32, 4, 1, 256, 256, 800, 40, [500] * 32)}
+
+
+@pytest.fixture(params=BASE)
+def base(request):
+    return BASE[request.param]
 
 
 def scaled(kf, qf, vf):
@@ -136,22 +149,22 @@ def scaled(kf, qf, vf):
 
 @pytest.mark.parametrize("kf,qf,vf", [(1e4, 1e-4, 1e-20), (1e-12, 1e12, 1e20), (3e-30, 3e29, 1.0),
                                       (1e-3, 1.0, 1e-3)])
-def test_chunk_magnitudes(cuda_device, kf, qf, vf):
-    run_both(*BASE, change=scaled(kf, qf, vf), vscale=vf)
+def test_chunk_magnitudes(cuda_device, base, kf, qf, vf):
+    run_both(*base, change=scaled(kf, qf, vf), vscale=vf)
 
 
-def test_chunk_growing_values(cuda_device):
+def test_chunk_growing_values(cuda_device, base):
     """V (and K) outgrow the first tile's scale again and again."""
     def change(q, K, V, kn, vn):
         V *= (2.0 ** (np.arange(V.shape[2]) // 50)).astype(np.float32)[None, None, :, None]
         vn *= np.float32(2.0 ** 11)
         K[:, :, 200:] *= 16
         q /= 16
-    run_both(*BASE, change=change, vscale=2.0 ** 11)
+    run_both(*base, change=change, vscale=2.0 ** 11)
 
 
 @pytest.mark.parametrize("small", ["V", "K"])
-def test_chunk_falling_values(cuda_device, small):
+def test_chunk_falling_values(cuda_device, base, small):
     """A tile of very large values first, then ordinary ones; q has no part in
     the large keys, so the ordinary ones decide."""
     def change(q, K, V, kn, vn):
@@ -167,11 +180,12 @@ def test_chunk_falling_values(cuda_device, small):
         else:
             K[:, :, :32] = 0
             K[:, :, :32, 0] = 1e12
-    run_both(*BASE, change=change)
+    run_both(*base, change=change)
 
 
 @pytest.mark.parametrize("where", ["k_neg_inf", "k_nan", "v_inf", "v_nan_new", "q_nan", "k_huge"])
-def test_chunk_non_finite(cuda_device, where):
+@pytest.mark.parametrize("shape", {**BASE, **MORE})
+def test_chunk_non_finite(cuda_device, where, shape):
     """A key of -inf has no weight, a NaN or an infinite value reaches the rows
     that see it and no others (rows before it in the chunk stay finite)."""
     def change(q, K, V, kn, vn):
@@ -190,15 +204,17 @@ def test_chunk_non_finite(cuda_device, where):
         else:
             K[0, 0, 100] = np.float32(3.3e38)
             q[...] = -np.abs(q)
-    B, h_q, h_kv, d_k, d_v, n_max, T, lens = BASE
-    q, K, V, kn, vn, ln = inputs(*BASE)
+    shape = {**BASE, **MORE}[shape]
+    B, h_q, h_kv, d_k, d_v, n_max, T, lens = shape
+    q, K, V, kn, vn, ln = inputs(*shape)
     change(q, K, V, kn, vn)
     sc = np.float32(d_k ** -0.5)
-    print("chunk non-finite", where, flush=True)
-    dl = dev(ln)
-    out = binding.decode_multi_step(dev(q), dev(K), dev(V), dev(kn), dev(vn), dl, float(sc))
+    print("chunk non-finite", where, shape[:7], flush=True)
+    dq, dK, dV, dl = dev(q), dev(K), dev(V), dev(ln)
+    step = binding.decode_multi_step(dq, dK, dV, dev(kn), dev(vn), dl, float(sc))
+    multi = binding.decode_multi(dq, dK, dV, dl, float(sc))   # the same positions again
     torch.cuda.synchronize()
-    got = out.cpu().numpy().astype(np.float64)[0]
+    outs = [x.cpu().numpy().astype(np.float64)[0] for x in (step, multi)]
     Kf, Vf = (np.concatenate([x[0, 0, :500], y[0, 0]]).astype(np.float64)
               for x, y in ((K, kn), (V, vn)))
     with np.errstate(all="ignore"):
@@ -212,10 +228,11 @@ def test_chunk_non_finite(cuda_device, where):
                 p[s == -np.inf] = 0
                 p /= p.sum()
                 ref = p @ Vf[:n]
-                assert np.array_equal(np.isnan(ref), np.isnan(got[h, r])), (h, r)
-                assert np.array_equal(np.isinf(ref), np.isinf(got[h, r])), (h, r)
                 ok = np.isfinite(ref)
-                assert not ok.any() or np.max(np.abs(ref[ok] - got[h, r][ok])) <= 1e-5, (h, r)
+                for got in outs:
+                    assert np.array_equal(np.isnan(ref), np.isnan(got[h, r])), (h, r)
+                    assert np.array_equal(np.isinf(ref), np.isinf(got[h, r])), (h, r)
+                    assert not ok.any() or np.max(np.abs(ref[ok] - got[h, r][ok])) <= 1e-5, (h, r)
 
 
 def test_chunk_replays_in_a_graph(cuda_device):
